@@ -63,7 +63,6 @@ template <class T>
 struct SweepArgs {
   void* B;                // transit buffer, cx<T>, nx/2 packed columns, tiled [y/TR][kx/TC][TR][TC]
   void* tA;               // state: t of the signal-side Fourier level (or t_white copy)
-  void* dA;               // state: d of that level (FK_ARRAY_STRIPE only)
   void* tB;               // state: t of the stripe level (FK_ARRAY_STRIPE only)
   const T* sc;            // [kx][ky] covariance of the chain's signal end
   const T* nbA;           // [kx][ky] Nbar of the array level

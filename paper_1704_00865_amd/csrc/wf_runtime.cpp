@@ -40,7 +40,6 @@ struct Ctx {
   int device = 0;
   void* B = nullptr;
   void* tA = nullptr;
-  void* dA = nullptr;
   void* tB = nullptr;
   void* sc = nullptr;
   void* nbA = nullptr;
@@ -111,7 +110,6 @@ void for_each_buffer(Ctx* c, F take) {
   const size_t modes = nh * ny;
   take((void**)&c->B, ny * (nx / 2) * 2 * esz);
   take((void**)&c->tA, modes * 2 * esz);
-  take((void**)&c->dA, modes * 2 * esz);
   take((void**)&c->tB, modes * 2 * esz);
   take((void**)&c->sc, modes * esz);
   take((void**)&c->nbA, modes * esz);
@@ -173,7 +171,7 @@ void make_table(std::vector<T>& out, int n) {
 }
 
 void free_ctx(Ctx* c) {
-  void* bufs[] = {c->B, c->tA, c->dA, c->tB, c->sc, c->nbA, c->sy, c->sig, c->nbar2, c->twx, c->twy,
+  void* bufs[] = {c->B, c->tA, c->tB, c->sc, c->nbA, c->sy, c->sig, c->nbar2, c->twx, c->twy,
                   c->Mx, c->My, c->part, c->jpart, c->stats, c->sch, c->lam, c->trace,
                   c->alpha_sk, c->d_args, c->d_margs, c->d_ctrl, c->ref_d, c->ref_npix,
                   c->ref_sk, c->ref_poof, c->ref_pst, c->ref_out, c->ref_init, c->ref_margs};
@@ -337,7 +335,6 @@ SweepArgs<T> sweep_args(Ctx* c, const wf_inputs* in, const Chain& ch) {
   SweepArgs<T> a{};
   a.B = c->B;
   a.tA = c->tA;
-  a.dA = c->dA;
   a.tB = c->tB;
   a.sc = (const T*)c->sc;
   a.nbA = (const T*)c->nbA;
@@ -488,7 +485,7 @@ wf_status map_setup(Ctx* c, const wf_inputs* in, const wf_schedule* s, const voi
   WF_TRY(launch_prep<T>((const T*)in->n_pix, in->mask, c->ny, c->nx, r.ch.phi + r.ch.tauW,
                         (T*)c->nbar2, (const T*)in->s_k, (const T*)in->p_oof,
                         (const T*)in->p_stripe, r.ch.pa, (T*)c->sc, (T*)c->nbA, (T*)c->sy,
-                        (T*)c->sig, c->B, c->tA, c->dA, c->tB, st));
+                        (T*)c->sig, c->B, c->tA, c->tB, st));
   // schedule: lambda per sweep and the device-side controller state
   const int K = s->monitor_every, maxs = s->max_sweeps;
   r.n_chunks = (maxs + K - 1) / K;
@@ -1002,7 +999,7 @@ wf_status solve_refined(Ctx* c32, Ctx* c64, const wf_inputs* in, const wf_schedu
   in32.p_stripe = in->p_stripe ? c32->ref_pst : nullptr;
   // monitor passes on the float64 context, x read directly from x_acc:
   // [0] residual and the next right-hand side, [1] output s = S x
-  void* xacc = c64->dA;
+  void* xacc = c64->tB;
   MonArgs<double> mh[2];
   for (int i = 0; i < 2; ++i) {
     mh[i] = mon_args<double>(c64, in, r64.ch);
