@@ -206,13 +206,16 @@ __device__ __forceinline__ void dft(cx<T>* u) {
   else if constexpr (R == 16) dft16<T, INV>(u);
 }
 
-// complex values held by each thread: 16 for powers of two, 12 for lengths
-// with a factor 3 (radices 4, 2 and 12 divide it; with 24 values and radix 8
+// complex values held by each thread: 16 for powers of two from 1024, 8 below
+// (a small map fills a fraction of the chip, and its sweep takes as long as
+// one thread's serial chain, which half the values shorten: a 256^2 float64
+// sweep took 36 us with 16 values and 22 with 8, a 512^2 one 25 and 17, a
+// 64^2 float32 one 23 and 16), 12 for lengths with a factor 3 (radices 4, 2 and 12 divide it; with 24 values and radix 8
 // a 1536-point transform filled one wave, whose 12 KB exchange buffer held
 // the kernels to 1.5-2 waves per SIMD)
 template <int N>
 struct elems {
-  static constexpr int value = (N % 3 == 0) ? 12 : 16;
+  static constexpr int value = (N % 3 == 0) ? 12 : (N < 1024 ? 8 : 16);
 };
 
 // Index map of one transform's LDS exchange buffer (N complex values, E per
@@ -253,10 +256,6 @@ struct ldsmap {
 // the lengths with a factor 3 comes last, so every earlier span is a power of two
 template <int N>
 struct plan;
-template <> struct plan<64> { static constexpr int r[5] = {16, 4, 1, 1, 1}; };
-template <> struct plan<128> { static constexpr int r[5] = {16, 8, 1, 1, 1}; };
-template <> struct plan<256> { static constexpr int r[5] = {16, 16, 1, 1, 1}; };
-template <> struct plan<512> { static constexpr int r[5] = {16, 8, 4, 1, 1}; };
 template <> struct plan<1024> { static constexpr int r[5] = {16, 16, 4, 1, 1}; };
 template <> struct plan<2048> { static constexpr int r[5] = {16, 16, 8, 1, 1}; };
 template <> struct plan<4096> { static constexpr int r[5] = {16, 16, 16, 1, 1}; };
@@ -273,6 +272,10 @@ struct plan_for {
   static constexpr int r0 = plan<N>::r[0], r1 = plan<N>::r[1], r2 = plan<N>::r[2], r3 = plan<N>::r[3],
                        r4 = plan<N>::r[4];
 };
+template <> struct plan_for<64, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 1, r3 = 1, r4 = 1; };
+template <> struct plan_for<128, 8> { static constexpr int r0 = 8, r1 = 4, r2 = 4, r3 = 1, r4 = 1; };
+template <> struct plan_for<256, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 4, r3 = 1, r4 = 1; };
+template <> struct plan_for<512, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 1, r4 = 1; };
 template <> struct plan_for<1024, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 4, r3 = 4, r4 = 1; };
 template <> struct plan_for<2048, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 4, r4 = 1; };
 template <> struct plan_for<4096, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 8, r4 = 1; };
