@@ -206,16 +206,17 @@ __device__ __forceinline__ void dft(cx<T>* u) {
   else if constexpr (R == 16) dft16<T, INV>(u);
 }
 
-// complex values held by each thread: 16 for powers of two from 1024, 8 below
-// (a small map fills a fraction of the chip, and its sweep takes as long as
-// one thread's serial chain, which half the values shorten: a 256^2 float64
-// sweep took 36 us with 16 values and 22 with 8, a 512^2 one 25 and 17, a
-// 64^2 float32 one 23 and 16), 12 for lengths with a factor 3 (radices 4, 2 and 12 divide it; with 24 values and radix 8
-// a 1536-point transform filled one wave, whose 12 KB exchange buffer held
-// the kernels to 1.5-2 waves per SIMD)
+// complex values held by each thread: 16 for powers of two from 1024, 4 below
+// (a small map fills a fraction of the chip and its sweep takes as long as one
+// thread's serial chain, which fewer values shorten although the transforms
+// pass through LDS more often: with 16, 8 and 4 values a 64^2 float32 sweep
+// took 23, 16 and 13 us, a 256^2 float64 one 36, 22 and 17, a 512^2 float64 one
+// 25, 17 and 16), 12 for lengths with a factor 3 (radices 4, 2 and 12 divide
+// it; with 24 values and radix 8 a 1536-point transform filled one wave, whose
+// 12 KB exchange buffer held the kernels to 1.5-2 waves per SIMD)
 template <int N>
 struct elems {
-  static constexpr int value = (N % 3 == 0) ? 12 : (N < 1024 ? 8 : 16);
+  static constexpr int value = (N % 3 == 0) ? 12 : (N < 1024 ? 4 : 16);
 };
 
 // Index map of one transform's LDS exchange buffer (N complex values, E per
@@ -266,16 +267,16 @@ template <> struct plan<1536> { static constexpr int r[5] = {4, 4, 4, 2, 12}; };
 constexpr int kE = 16;  // values per thread for power-of-two lengths
 
 // radix plan for a transform spread over E values per thread: the default
-// plan, or (E = 8) radices of at most 8
+// plan, or radices of at most E
 template <int N, int E>
 struct plan_for {
   static constexpr int r0 = plan<N>::r[0], r1 = plan<N>::r[1], r2 = plan<N>::r[2], r3 = plan<N>::r[3],
                        r4 = plan<N>::r[4];
 };
-template <> struct plan_for<64, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 1, r3 = 1, r4 = 1; };
-template <> struct plan_for<128, 8> { static constexpr int r0 = 8, r1 = 4, r2 = 4, r3 = 1, r4 = 1; };
-template <> struct plan_for<256, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 4, r3 = 1, r4 = 1; };
-template <> struct plan_for<512, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 1, r4 = 1; };
+template <> struct plan_for<64, 4> { static constexpr int r0 = 4, r1 = 4, r2 = 4, r3 = 1, r4 = 1; };
+template <> struct plan_for<128, 4> { static constexpr int r0 = 4, r1 = 4, r2 = 4, r3 = 2, r4 = 1; };
+template <> struct plan_for<256, 4> { static constexpr int r0 = 4, r1 = 4, r2 = 4, r3 = 4, r4 = 1; };
+template <> struct plan_for<512, 4> { static constexpr int r0 = 4, r1 = 4, r2 = 4, r3 = 4, r4 = 2; };
 template <> struct plan_for<1024, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 4, r3 = 4, r4 = 1; };
 template <> struct plan_for<2048, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 4, r4 = 1; };
 template <> struct plan_for<4096, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 8, r4 = 1; };

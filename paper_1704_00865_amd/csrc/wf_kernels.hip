@@ -799,7 +799,7 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
   // short lengths' three waves per SIMD), or 2 with 8 values per thread from
   // 1024 points (four waves per SIMD leave 128 registers) and with 12 float32
   // values (three waves, 168 registers)
-  constexpr int HB = ((E == 8 && NY >= 1024) || (E == 12 && sizeof(T) == 4))
+  constexpr int HB = E == 4 ? 4 : ((E == 8 && NY >= 1024) || (E == 12 && sizeof(T) == 4))
                          ? 2
                          : ((sizeof(T) == 8 || E == 8 || E % 8 != 0 || NY >= 4096) ? 4 : 8);
   static_assert(E % HB == 0, "batches split the thread's values evenly");
