@@ -480,14 +480,6 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
   constexpr bool JV = MODE == ROW_SWEEP_J;
   T lt = (T)0;  // lambda * tau of the white level
   bool jdo = false;  // this sweep closes its chunk: sum the pixel term of J
-  if constexpr (SW) {
-    const WF_GLOBAL DevSched* s = gmem(a.sch);
-    if (s->done) return;
-    const int kk = s->base + k_local;
-    if (kk >= s->max_sweeps) return;
-    lt = (T)(gmem(a.lam)[kk] * a.tauW);
-    if constexpr (JV) jdo = kk == min(s->base + s->K, s->max_sweeps) - 1;
-  }
   __shared__ double jsh[JV ? 16 : 1];
   double jacc = 0.0;
   const int tid = threadIdx.x;
@@ -500,6 +492,30 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
   const int ya = y0 + 2 * p;
   constexpr int NTHR = RP * NT;  // threads of the block
   cx<T> reg[E];
+
+  // the white level's data and coefficients of this thread's pixels, in batches
+  // of 8 (float32) or 4 (float64, or 12 values per thread) to stay within the
+  // register budget; below 1024 points, where a launch waits on latency, all at
+  // once together with the band (with the same in the column kernel, the
+  // schedule read after the loads and the packed column in line: a 64^2
+  // float32 sweep 13.0 to 11.6 us, a 512^2 float64 one 16.4 to 15.7; from 1024
+  // points on early loads delay the band, 15.2 to 17.4 us at 2048)
+  constexpr int QB = (sizeof(T) == 8 || E % 8 != 0) ? 4 : 8;
+  static_assert(E % QB == 0, "batches split the thread's values evenly");
+  constexpr bool PIX_EARLY = E == QB && NX < 1024;
+  const WF_GLOBAL T* gd = gmem(a.d);
+  const WF_GLOBAL T* gn2 = gmem(a.nbar2);
+  T dv0[QB], dv1[QB], nb0[QB], nb1[QB];
+  auto load_pix = [&](int h) {
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const size_t i0 = (size_t)ya * NX + t + NT * (h + q);
+      dv0[q] = gd[i0];
+      dv1[q] = gd[i0 + NX];
+      nb0[q] = gn2[i0];
+      nb1[q] = gn2[i0 + NX];
+    }
+  };
 
   if constexpr (SW || MODE == ROW_C2R) {
     // every load of the band and of the twiddle table is issued before the
@@ -515,6 +531,16 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
     }
     TwiddleStage<T, NX, E, NTHR> tws;
     if constexpr (LTW) tws.load(twg, tid);
+    if constexpr (SW && PIX_EARLY) load_pix(0);
+    if constexpr (SW) {
+      // (after the loads: the schedule is two dependent reads)
+      const WF_GLOBAL DevSched* s = gmem(a.sch);
+      if (s->done) return;
+      const int kk = s->base + k_local;
+      if (kk >= s->max_sweeps) return;
+      lt = (T)(gmem(a.lam)[kk] * a.tauW);
+      if constexpr (JV) jdo = kk == min(s->base + s->K, s->max_sweeps) - 1;
+    }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const int e = (tid + it * NTHR) * EPC;
@@ -560,24 +586,10 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
       }
       return;
     } else {
-      // white-level update, data and coefficients loaded in batches of 8
-      // (float32) or 4 (float64, or 12 values per thread) values, to stay
-      // within the register budget
-      constexpr int QB = (sizeof(T) == 8 || E % 8 != 0) ? 4 : 8;
-      static_assert(E % QB == 0, "batches split the thread's values evenly");
-      const WF_GLOBAL T* gd = gmem(a.d);
-      const WF_GLOBAL T* gn2 = gmem(a.nbar2);
+      // white-level update
 #pragma unroll
       for (int h = 0; h < E; h += QB) {
-        T dv0[QB], dv1[QB], nb0[QB], nb1[QB];
-#pragma unroll
-        for (int q = 0; q < QB; ++q) {
-          const size_t i0 = (size_t)ya * NX + t + NT * (h + q);
-          dv0[q] = gd[i0];
-          dv1[q] = gd[i0 + NX];
-          nb0[q] = gn2[i0];
-          nb1[q] = gn2[i0 + NX];
-        }
+        if constexpr (!PIX_EARLY) load_pix(h);
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
           const T d1a = reg[h + q].re * sc, d1b = reg[h + q].im * sc;
@@ -694,20 +706,21 @@ __device__ __forceinline__ cx<T> chain_d0(const ChainCoef<T>& k, T s, T nbA, cx<
 }
 
 // One mode: t_2 (white messenger, Fourier) in, field for the white level out.
-// Reads and writes the stored Fourier-side fields of this mode.  With JV, adds
+// Reads and writes the stored Fourier-side fields of this mode.  pst: the
+// stripe variance of a mode on the k_x = 0 column, else 0.  With JV, adds
 // jw times this mode's terms of the joint objective (unnormalised
 // coefficients; the caller applies 1/(nx ny)) to jacc.
 template <class T, int FK, bool JV>
 __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>* tB,
-                                            const ChainCoef<T>& k, int kx, int ky, size_t idx,
-                                            cx<T> t2, T s, T nbA, T pst, cx<T> tAo, cx<T> tBo,
-                                            double& jacc, double jw) {
+                                            const ChainCoef<T>& k, size_t idx, cx<T> t2, T s,
+                                            T nbA, T pst, cx<T> tAo, cx<T> tBo, double& jacc,
+                                            double jw) {
   if constexpr (FK == FK_NONE) {
     if (k.store_first) stc(tA + idx, t2);
     if constexpr (JV) jacc += jw * cnorm2(t2) / ((double)s + k.jTW);
     return cscale(t2, s * rcp(s + k.TW));
   } else if constexpr (FK == FK_ARRAY_STRIPE) {
-    const T nbB = (kx == 0 ? k.nxr * pst : (T)0) + k.cB;
+    const T nbB = k.nxr * pst + k.cB;
     const cx<T> dAo = chain_d0(k, s, nbA, tAo, tBo);
     const cx<T> dBn = wavg(nbB, t2, k.TW, tBo, rcp(nbB + k.TW));
     const cx<T> tBn = wavg(k.TB, dBn, nbB, dAo, rcp(nbB + k.TB));
@@ -725,7 +738,7 @@ __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>
     // one Fourier level: an array level or the stripe level
     T nb;
     if constexpr (FK == FK_ARRAY) nb = nbA;
-    else nb = (kx == 0 ? k.nxr * pst : (T)0) + k.cB;
+    else nb = k.nxr * pst + k.cB;
     const cx<T> dAn = wavg(nb, t2, k.TW, tAo, rcp(nb + k.TW));
     const cx<T> so = cscale(tAo, s * rcp(s + k.SA));
     const cx<T> tAn = wavg(k.TA, dAn, nb, so, rcp(nb + k.TA));
@@ -761,20 +774,6 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
   double lam = 0.0, lamp = 0.0, lampp = 0.0;
   bool first = false;
   bool store_first = false;  // the chunk's last sweep (also: sum J there)
-  if constexpr (SW) {
-    const WF_GLOBAL DevSched* s = gmem(a.sch);
-    if (s->done) return;
-    const int base = s->base;
-    const int kk = base + k_local;
-    if (kk >= s->max_sweeps) return;
-    const WF_GLOBAL double* glam = gmem(a.lam);
-    lam = glam[kk];
-    lamp = glam[kk > 0 ? kk - 1 : 0];
-    lampp = glam[kk > 1 ? kk - 2 : 0];
-    first = kk == 0;
-    const int klast = min(base + s->K, s->max_sweeps) - 1;
-    store_first = (kk == klast);
-  }
   const int tid = threadIdx.x;
   const int G = a.nx / 2 / TC;
   const int g = xcd_remap(blockIdx.x, G, lines_share<T>(TRTC));
@@ -810,18 +809,30 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
   const cx<T> z0 = {(T)0, (T)0};
   T sv[HB], nv[HB], pv[HB];
   cx<T> ta[HB], tb[HB];
+  // The packed column's threads hold, in place of a column's modes q < E, the
+  // modes q < E/2 of k_x = 0 and, in slots q >= E/2, of k_x = nx/2: the two
+  // real columns are Hermitian in k_y, so the chain runs on k_y <= NY/2 of
+  // each, in the same instructions as any other column (block 0 is no
+  // straggler), and the rest follows by conjugation.  The stored fields of
+  // k_y > NY/2 in these columns are not updated (readers take the mirrored
+  // mode).
+  constexpr int EH = E / 2;
+  auto slot_ky = [&](int q) { return t + NT * (packed && q >= EH ? q - EH : q); };
+  auto slot_idx = [&](int q) { return (size_t)(packed && q >= EH ? kxn : kxc) * NY + slot_ky(q); };
   auto load_half = [&](int h) {
 #pragma unroll
     for (int q = 0; q < HB; ++q) {
-      const int ky = t + NT * (h + q);
-      const size_t idx = (size_t)kxc * NY + ky;
+      const size_t idx = slot_idx(h + q);
       sv[q] = gsc[idx];
       nv[q] = needNb ? gnb[idx] : (T)0;
-      pv[q] = needP ? gps[ky] : (T)0;
+      pv[q] = (needP && packed && h + q < EH) ? gps[slot_ky(h + q)] : (T)0;
       ta[q] = hasA ? ldc(gtA + idx) : z0;
       tb[q] = hasB ? ldc(gtB + idx) : z0;
     }
   };
+  // below 1024 points, where a launch waits on latency, all modes are loaded
+  // together with the columns
+  constexpr bool EARLY = SW && E == HB && NY < 1024;
 
   if constexpr (MODE == COL_INV_IN) {
     if constexpr (LTW) stage_twiddles<T, NY, E, NTHR>(twl, twg, tid);
@@ -855,6 +866,22 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
     }
     TwiddleStage<T, NY, E, NTHR> tws;
     if constexpr (LTW) tws.load(twg, tid);
+    if constexpr (EARLY) load_half(0);
+    if constexpr (SW) {
+      // (after the loads: the schedule is two dependent reads)
+      const WF_GLOBAL DevSched* s = gmem(a.sch);
+      if (s->done) return;
+      const int base = s->base;
+      const int kk = base + k_local;
+      if (kk >= s->max_sweeps) return;
+      const WF_GLOBAL double* glam = gmem(a.lam);
+      lam = glam[kk];
+      lamp = glam[kk > 0 ? kk - 1 : 0];
+      lampp = glam[kk > 1 ? kk - 2 : 0];
+      first = kk == 0;
+      const int klast = min(base + s->K, s->max_sweeps) - 1;
+      store_first = (kk == klast);
+    }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const int e = (tid + it * NTHR) * EPC;
@@ -875,10 +902,31 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
   }
 
   // packed column (block 0, column 0): split Z = C0 + i CN into the k_x = 0
-  // and k_x = nx/2 spectra; C0 stays in registers, CN goes to this column's
-  // LDS slots (only this column's threads touch them until the inverse FFT)
+  // and k_x = nx/2 spectra
   cx<T>* cnl = lds;  // column 0's region
-  if constexpr (MODE != COL_INV_IN) {
+  cx<T> zmid = {(T)0, (T)0};  // Z at k_y = NY/2 (thread 0 of the packed column)
+  if constexpr (SW) {
+    // both spectra for k_y < NY/2, in the slots described above
+    if (g == 0) {
+      if (packed) {
+#pragma unroll
+        for (int q = EH; q < E; ++q) lds[LM::at_tq(t, q)] = reg[q];
+      }
+      __syncthreads();
+      if (packed) {
+        zmid = reg[EH];
+#pragma unroll
+        for (int q = 0; q < EH; ++q) {
+          const int ky = t + NT * q;
+          const cx<T> zk = reg[q], zm = ky == 0 ? zk : lds[LM::at(NY - ky)];
+          reg[q] = cx<T>{(zk.re + zm.re) * (T)0.5, (zk.im - zm.im) * (T)0.5};
+          reg[q + EH] = cx<T>{(zk.im + zm.im) * (T)0.5, (zm.re - zk.re) * (T)0.5};
+        }
+      }
+    }
+  } else if constexpr (MODE != COL_INV_IN) {
+    // C0 stays in registers, CN goes to this column's LDS slots (only this
+    // column's threads touch them until the inverse FFT)
     if (g == 0) {
       if (packed) {
 #pragma unroll
@@ -933,96 +981,51 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
     k.jTB = lam * a.tauB;
     // J only on the chunk's last sweep (block-uniform)
     const bool jdo = JV && store_first;
-    const cx<T> z = {(T)0, (T)0};
-    if (!packed) {
-      // this column, in batches of loads
 #pragma unroll
-      for (int h = 0; h < E; h += HB) {
-        load_half(h);
+    for (int h = 0; h < E; h += HB) {
+      if constexpr (!EARLY) load_half(h);
 #pragma unroll
-        for (int q = 0; q < HB; ++q) {
-          const int ky = t + NT * (h + q);
-          const size_t idx = (size_t)kxc * NY + ky;
-          if (jdo)
-            reg[h + q] = chain_mode<T, FK, JV>(gtA, gtB, k, kxc, ky, idx, reg[h + q], sv[q],
-                                               nv[q], pv[q], ta[q], tb[q], jacc, 2.0);
-          else
-            reg[h + q] = chain_mode<T, FK, false>(gtA, gtB, k, kxc, ky, idx, reg[h + q],
-                                                  sv[q], nv[q], pv[q], ta[q], tb[q], jacc,
-                                                  0.0);
-        }
+      for (int q = 0; q < HB; ++q) {
+        const size_t idx = slot_idx(h + q);
+        // k_y and NY - k_y of a real column are one conjugate pair
+        if (jdo)
+          reg[h + q] = chain_mode<T, FK, JV>(gtA, gtB, k, idx, reg[h + q], sv[q], nv[q], pv[q],
+                                             ta[q], tb[q], jacc,
+                                             packed && slot_ky(h + q) == 0 ? 1.0 : 2.0);
+        else
+          reg[h + q] = chain_mode<T, FK, false>(gtA, gtB, k, idx, reg[h + q], sv[q], nv[q], pv[q],
+                                                ta[q], tb[q], jacc, 0.0);
       }
     }
     if (g == 0) {
-      // the packed column: the real-valued columns k_x = 0 (C0, in registers)
-      // and k_x = nx/2 (CN, in this column's LDS slots) are Hermitian in k_y,
-      // so the chain runs on k_y <= NY/2 only -- as many modes per thread as
-      // any other column, so this block is no straggler -- and the rest
-      // follows by conjugation.  The stored fields of k_y > NY/2 in these two
-      // columns are not updated (readers take the mirrored mode).
-      constexpr int EH = E / 2;  // registers q < EH hold k_y < NY/2
+      // k_y = NY/2 of the two real columns: threads 0 (k_x = 0) and 1 (nx/2)
+      if (packed && t < 2) {
+        const size_t idx = (size_t)(t == 0 ? 0 : kxn) * NY + NY / 2;
+        const T zi = __shfl(zmid.im, threadIdx.x & 62, 64);
+        const cx<T> c = {t == 0 ? zmid.re : zi, (T)0};
+        const cx<T> v = chain_mode<T, FK, JV>(
+            gtA, gtB, k, idx, c, gsc[idx], needNb ? gnb[idx] : (T)0,
+            needP && t == 0 ? gps[NY / 2] : (T)0, hasA ? ldc(gtA + idx) : z0,
+            hasB ? ldc(gtB + idx) : z0, jacc, jdo ? 1.0 : 0.0);
+        const T nr = __shfl_xor(v.re, 1, 64), ni = __shfl_xor(v.im, 1, 64);
+        zmid = cx<T>{v.re - ni, v.im + nr};
+      }
+      // Z = C0 + i CN again: k_y < NY/2 in its own registers, NY - k_y through
+      // LDS
       if (packed) {
-        // both columns' coefficients and fields of PB modes, loaded before the
-        // first store of the batch (a load behind a store waits for memory
-        // each time: this block's serial chain is the whole launch on a small
-        // map)
-        constexpr int PB = EH % HB == 0 ? HB : EH / 2;
-        static_assert(EH % PB == 0, "batches split the half column evenly");
-        T psv[PB], s0[PB], sN[PB], n0[PB], nN[PB];
-        cx<T> ta0[PB], taN[PB], tb0[PB], tbN[PB];
-        auto load_pair = [&](int u, int ky) {
-          const size_t i0 = (size_t)ky, iN = (size_t)kxn * NY + ky;
-          psv[u] = needP ? gps[ky] : (T)0;
-          s0[u] = gsc[i0];
-          sN[u] = gsc[iN];
-          n0[u] = needNb ? gnb[i0] : (T)0;
-          nN[u] = needNb ? gnb[iN] : (T)0;
-          ta0[u] = hasA ? ldc(gtA + i0) : z;
-          taN[u] = hasA ? ldc(gtA + iN) : z;
-          tb0[u] = hasB ? ldc(gtB + i0) : z;
-          tbN[u] = hasB ? ldc(gtB + iN) : z;
-        };
-        auto pair = [&](int u, int q) {
+#pragma unroll
+        for (int q = 0; q < EH; ++q) {
           const int ky = t + NT * q;
-          const int li = LM::at_tq(t, q);
-          const size_t i0 = (size_t)ky, iN = (size_t)kxn * NY + ky;
-          // k_y and NY - k_y of a real column are one conjugate pair; the
-          // terms are summed (weight > 0) on the chunk's last sweep only
-          const double jw = !jdo ? 0.0 : ((ky == 0 || ky == NY / 2) ? 1.0 : 2.0);
-          reg[q] = chain_mode<T, FK, JV>(gtA, gtB, k, 0, ky, i0, reg[q], s0[u], n0[u], psv[u],
-                                         ta0[u], tb0[u], jacc, jw);
-          cnl[li] = chain_mode<T, FK, JV>(gtA, gtB, k, kxn, ky, iN, cnl[li], sN[u], nN[u], psv[u],
-                                          taN[u], tbN[u], jacc, jw);
-          // C0 of k_y in (0, NY/2) waits in the unused CN slot of NY - k_y
-          if (q < EH && ky > 0) cnl[LM::at(NY - ky)] = reg[q];
-        };
-#pragma unroll
-        for (int h = 0; h < EH; h += PB) {
-#pragma unroll
-          for (int u = 0; u < PB; ++u) load_pair(u, t + NT * (h + u));
-#pragma unroll
-          for (int u = 0; u < PB; ++u) pair(u, h + u);
+          const cx<T> c0 = reg[q], cn = reg[q + EH];
+          reg[q] = cx<T>{c0.re - cn.im, c0.im + cn.re};
+          if (ky > 0) lds[LM::at(NY - ky)] = cx<T>{c0.re + cn.im, cn.re - c0.im};
         }
-        if (t == 0) {  // k_y = NY/2
-          load_pair(0, NT * EH);
-          pair(0, EH);
-        }
+        if (t == 0) lds[LM::at(NY / 2)] = zmid;
       }
       __syncthreads();
       if (packed) {
 #pragma unroll
-        for (int q = 0; q < E; ++q) {
-          const int ky = t + NT * q;
-          cx<T> c0, cn;
-          if (ky <= NY / 2) {
-            c0 = reg[q];
-            cn = cnl[LM::at_tq(t, q)];
-          } else {
-            c0 = cconj(cnl[LM::at_tq(t, q)]);
-            cn = cconj(cnl[LM::at(NY - ky)]);
-          }
-          reg[q] = cx<T>{c0.re - cn.im, c0.im + cn.re};
-        }
+        for (int q = EH; q < E; ++q) reg[q] = lds[LM::at_tq(t, q)];
       }
     }
   }
