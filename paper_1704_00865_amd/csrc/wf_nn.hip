@@ -5,9 +5,8 @@
 // Every 3x3 convolution is an implicit GEMM on v_mfma_f32_16x16x32_bf16:
 // output pixels are the rows, output channels the columns and (tap, input
 // channel) the reduction.  Activations are [pixel][channel] bfloat16 so that
-// one lane's eight consecutive reduction values are one 16-byte load; the
-// periodic neighbour of each pixel is computed per tap, so no halo copies
-// are made.  The weight gradient is the same product with pixels as the
+// one lane's eight consecutive reduction values are one 16-byte load; a block
+// stages its pixels with their periodic border in LDS.  The weight gradient is the same product with pixels as the
 // reduction: 64-pixel slabs of the input and of the output gradient are
 // staged transposed in LDS, each block sums one pixel chunk, and a second
 // kernel adds the chunks in a fixed order (deterministic).
@@ -26,6 +25,7 @@ namespace wfnn {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLevels = 4;
 constexpr int kChan[kLevels] = {32, 64, 96, 128};
@@ -34,110 +34,231 @@ constexpr int kPad = 32;  // channels of the padded input and output
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// round to nearest even; NaN stays NaN
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+// round to nearest even (v_cvt_pk_bf16_f32); NaN stays NaN
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 __device__ __forceinline__ int wrap(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
+// eight bfloat16 values <-> float
+__device__ __forceinline__ void unpack8(u32x4 v, float* f) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    f[2 * e] = __uint_as_float(v[e] << 16);
+    f[2 * e + 1] = __uint_as_float(v[e] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ u32x4 pack8(const float* f) {
+  u32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = (uint32_t)f2bf(f[2 * e]) | ((uint32_t)f2bf(f[2 * e + 1]) << 16);
+  return v;
+}
+// v where m > 0, else 0, on 8 bfloat16 values
+__device__ __forceinline__ u32x4 mask8(u32x4 v, u32x4 m) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t lo = __uint_as_float(m[e] << 16) > 0.f ? 0xffffu : 0u;
+    const uint32_t hi = __uint_as_float(m[e] & 0xffff0000u) > 0.f ? 0xffff0000u : 0u;
+    v[e] &= lo | hi;
+  }
+  return v;
+}
 
 // ---------------------------------------------------------------------------
 // convolution (forward, and the input adjoint with mirrored taps)
 // ---------------------------------------------------------------------------
 
 struct ConvArgs {
-  const uint16_t* in;  // [P][cin]
-  const uint16_t* wt;  // [9][cout][cin]: reduction dimension contiguous
-  const float* bias;   // [cout] or null
-  uint16_t* out;       // [P][cout] or null
-  float* out_f32;      // [P]: channel 0 in float32, or null
-  int h, w, cin, cout;
-  int flip;            // 1: tap (dy, dx) reads the pixel at (-dy, -dx)
+  const uint16_t* in;    // [P][CIN]; with up: [P/4][CIN], read at (y/2, x/2)
+  const uint16_t* wt;    // [9][cout][CIN]: reduction dimension contiguous
+  const float* bias;     // [cout] or null
+  uint16_t* out;         // [P][cout] or null: v = conv + bias (ReLU with relu)
+  uint16_t* out2;        // [P][cout] or null: v + skip, or v where mask > 0
+  const uint16_t* skip;  // [P][cout] or null
+  const uint16_t* mask;  // [P][cout] or null; without out2 it applies to out
+  float* out_f32;        // [P]: channel 0 in float32, or null
+  int h, w, cout;
+  int up;
+  int flip;              // 1: tap (dy, dx) reads the pixel at (-dy, -dx)
   int relu;
-  int64_t P;           // pixels
 };
 
-// Block: 256 threads, 128 pixels x COT output channels; wave w owns pixels
-// 32w..32w+31 of the block (two 16-row tiles) and every column tile, so each
-// weight fragment feeds two MFMAs.  One tap's weights (COT x cin) are staged
-// in LDS and shared by the four waves.  Pixels past the end (P not a multiple
-// of 128) read a valid pixel and store nothing.
-template <int COT>
+// Tile of one block (256 threads): 4 MT sixteen-pixel rows of the product, as
+// TH image rows of TW pixels, times COT output channels; wave v owns MT of the
+// sixteen-pixel rows and every column tile.  The tile's input with its
+// one-pixel border is staged in LDS once, whole, and each of the nine taps
+// reads it shifted (a tap per global read took the input nine times through
+// the caches and waited for it each time); the weights of NTB taps at a time
+// are staged beside it, the next group's loads in flight meanwhile.  Both are
+// padded by 16 bytes per row: sixteen lanes' 16-byte reads fall on distinct
+// banks.  Bound: at full resolution (32 channels) memory, one read and one
+// write of the activations: four 1024^2 maps 269 to 166 us per launch (0.54
+// GB, 3.2 TB/s); with more channels LDS reads and matrix instructions, about
+// level.  Products are summed tap by tap, then channel by channel.
+template <int CIN, int COT, int TW, int MT>
+struct conv_tile {
+  static constexpr int TH = 4 * MT * 16 / TW;
+  static constexpr int HP = (TH + 2) * (TW + 2);  // staged pixels
+  static constexpr int PS = CIN + 8;              // LDS row of a pixel or of a weight
+  static constexpr int TAP = COT * PS;            // one tap's weights
+  static constexpr int room = 78 * 1024 / 2 - HP * PS;
+  static constexpr int NTB = 9 * TAP <= room ? 9 : (3 * TAP <= room ? 3 : 1);
+  static constexpr int OS = COT + 8;              // LDS row of an output pixel
+  static constexpr int main = HP * PS + NTB * TAP, epi = TH * TW * OS;
+  static constexpr int lds = main > epi ? main : epi;
+};
+
+template <int CIN, int COT, int TW, int MT>
 __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
-  constexpr int NJ = COT / 16;
-  constexpr int WS = 128 + 8;  // LDS row: up to 128 input channels + pad
-  __shared__ __attribute__((aligned(16))) uint16_t ws[COT * WS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  using C = conv_tile<CIN, COT, TW, MT>;
+  constexpr int NJ = COT / 16, TH = C::TH, PS = C::PS, NTB = C::NTB, U = CIN / 8;
+  __shared__ __attribute__((aligned(16))) uint16_t sm[C::lds];
+  uint16_t* xs = sm;
+  uint16_t* ws = sm + C::HP * PS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kq = lane >> 4;
-  const int64_t pw = (int64_t)blockIdx.x * 128 + wave * 32;
   const int co0 = blockIdx.y * COT;
+  // consecutive tiles of an image run on one XCD (their borders overlap)
+  const int nt = gridDim.x;
+  const int tile = nt % 8 == 0 ? (int)(blockIdx.x & 7) * (nt / 8) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int tx = a.w / TW, ty = a.h / TH;
+  const int img = tile / (tx * ty), rem = tile - img * (tx * ty);
+  const int y0 = rem / tx * TH, x0 = (rem - rem / tx * tx) * TW;
   const int hw = a.h * a.w;
-  int64_t img[2];
-  int yy0[2], xx0[2];
+
+  // weights of taps NTB s .. NTB s + NTB - 1, in flight in registers
+  constexpr int WN = NTB * COT * U, WU = (WN + 255) / 256;
+  u32x4 wr[WU];
+  auto wload = [&](int s) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    int64_t p = pw + 16 * u + r;
-    if (p >= a.P) p = a.P - 1;
-    img[u] = p / hw;
-    const int rem = (int)(p - img[u] * hw);
-    yy0[u] = rem / a.w;
-    xx0[u] = rem - yy0[u] * a.w;
-  }
-  f32x4 acc[2][NJ];
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int c8 = a.cin / 8;
-  for (int t = 0; t < 9; ++t) {
-    __syncthreads();  // the previous tap's weights have been consumed
-    for (int i = threadIdx.x; i < COT * c8; i += 256) {
-      const int co = i / c8, cc = i - co * c8;
-      *(uint4*)&ws[co * WS + cc * 8] =
-          *(const uint4*)(a.wt + ((int64_t)t * a.cout + co0 + co) * a.cin + cc * 8);
+    for (int k = 0; k < WU; ++k) {
+      const int i = min(tid + k * 256, WN - 1);
+      const int row = i / U, cc = i - row * U, t = row / COT, co = row - t * COT;
+      wr[k] = *(const u32x4*)(a.wt + ((int64_t)(NTB * s + t) * a.cout + co0 + co) * CIN + cc * 8);
     }
-    __syncthreads();
-    int dy = t / 3 - 1, dx = t % 3 - 1;
-    if (a.flip) {
-      dy = -dy;
-      dx = -dx;
-    }
-    const uint16_t* arow[2];
+  };
+  auto wstore = [&]() {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int yy = wrap(yy0[u] + dy, a.h), xx = wrap(xx0[u] + dx, a.w);
-      arow[u] = a.in + (img[u] * hw + (int64_t)yy * a.w + xx) * a.cin + kq * 8;
+    for (int k = 0; k < WU; ++k) {
+      const int i = tid + k * 256;
+      const int row = i / U, cc = i - row * U;
+      if (i < WN) *(u32x4*)&ws[row * PS + cc * 8] = wr[k];
     }
-    for (int c = 0; c < a.cin; c += 32) {
-      const bf16x8 a0 = __builtin_bit_cast(bf16x8, *(const uint4*)(arow[0] + c));
-      const bf16x8 a1 = __builtin_bit_cast(bf16x8, *(const uint4*)(arow[1] + c));
+  };
+  wload(0);
+  {
+    constexpr int N = C::HP * U, NU = (N + 255) / 256, G = 6;
+    const int ih = a.up ? a.h >> 1 : a.h, iw = a.up ? a.w >> 1 : a.w;
+    const uint16_t* src = a.in + (int64_t)img * ih * iw * CIN;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const bf16x8 bv = __builtin_bit_cast(bf16x8, *(const uint4*)&ws[(16 * j + r) * WS + c + kq * 8]);
-        acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bv, acc[0][j], 0, 0, 0);
-        acc[1][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bv, acc[1][j], 0, 0, 0);
+    for (int k0 = 0; k0 < NU; k0 += G) {
+      u32x4 v[G];
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const int i = min(tid + (k0 + k) * 256, N - 1);
+        const int px = i / U, cc = i - px * U;
+        const int yy = wrap(y0 - 1 + px / (TW + 2), a.h), xx = wrap(x0 - 1 + px % (TW + 2), a.w);
+        if (k0 + k < NU)
+          v[k] = *(const u32x4*)(src + ((int64_t)(yy >> a.up) * iw + (xx >> a.up)) * CIN + cc * 8);
+      }
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const int i = tid + (k0 + k) * 256;
+        const int px = i / U, cc = i - px * U;
+        if (k0 + k < NU && i < N) *(u32x4*)&xs[px * PS + cc * 8] = v[k];
       }
     }
   }
-  // lane holds rows 4 kq + v (pixels) of column r (channel) of each tile
+  f32x4 acc[MT][NJ];
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // staged pixel of this lane's row of product row u, before the tap's shift
+  int prow[MT];
+#pragma unroll
+  for (int u = 0; u < MT; ++u) {
+    const int m = wave * MT + u;  // product row: 16 / TW image rows
+    prow[u] = (1 + m * (16 / TW) + r / TW) * (TW + 2) + 1 + r % TW;
+  }
+#pragma unroll 1
+  for (int s = 0; s < 9 / NTB; ++s) {
+    if (s > 0) __syncthreads();  // the previous taps' weights have been consumed
+    wstore();
+    __syncthreads();
+    if (s + 1 < 9 / NTB) wload(s + 1);
+#pragma unroll
+    for (int tt = 0; tt < NTB; ++tt) {
+      const int t = NTB * s + tt;
+      int dy = t / 3 - 1, dx = t % 3 - 1;
+      if (a.flip) {
+        dy = -dy;
+        dx = -dx;
+      }
+      const int sh = dy * (TW + 2) + dx;
+#pragma unroll
+      for (int c = 0; c < CIN; c += 32) {
+        bf16x8 av[MT];
+#pragma unroll
+        for (int u = 0; u < MT; ++u)
+          av[u] = __builtin_bit_cast(bf16x8, *(const u32x4*)&xs[(prow[u] + sh) * PS + c + kq * 8]);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const bf16x8 bv = __builtin_bit_cast(
+              bf16x8, *(const u32x4*)&ws[(tt * COT + 16 * j + r) * PS + c + kq * 8]);
+#pragma unroll
+          for (int u = 0; u < MT; ++u)
+            acc[u][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u], bv, acc[u][j], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // lane holds rows 4 kq + v (pixels) of column r (channel) of each tile; the
+  // bfloat16 tile goes through LDS so that memory sees whole 16-byte vectors
+  __syncthreads();
+  constexpr int OS = C::OS;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int co = co0 + 16 * j + r;
     const float bb = a.bias ? a.bias[co] : 0.f;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < MT; ++u)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t pp = pw + 16 * u + 4 * kq + v;
-        if (pp >= a.P) continue;
+        const int pp = (wave * MT + u) * 16 + 4 * kq + v;  // pixel of the tile, row-major
         float val = acc[u][j][v] + bb;
         if (a.relu) val = fmaxf(val, 0.f);
-        if (a.out) a.out[pp * a.cout + co] = f2bf(val);
-        if (a.out_f32 && co == 0) a.out_f32[pp] = val;
+        sm[pp * OS + 16 * j + r] = f2bf(val);
+        if (a.out_f32 && co == 0)
+          a.out_f32[(int64_t)img * hw + (int64_t)(y0 + pp / TW) * a.w + x0 + pp % TW] = val;
       }
+  }
+  if (!a.out && !a.out2) return;
+  __syncthreads();
+  constexpr int VN = TH * TW * (COT / 8);
+#pragma unroll 2
+  for (int i = tid; i < VN; i += 256) {
+    const int pp = i / (COT / 8), cc = i - pp * (COT / 8);
+    const int64_t g = ((int64_t)img * hw + (int64_t)(y0 + pp / TW) * a.w + x0 + pp % TW) * a.cout +
+                      co0 + cc * 8;
+    const u32x4 v = *(const u32x4*)&sm[pp * OS + cc * 8];
+    u32x4 q = v;
+    if (a.skip) {
+      float f[8], k[8];
+      unpack8(v, f);
+      unpack8(*(const u32x4*)(a.skip + g), k);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] += k[e];
+      q = pack8(f);
+    } else if (a.mask) {
+      q = mask8(v, *(const u32x4*)(a.mask + g));
+    }
+    if (a.out2) {
+      *(u32x4*)(a.out2 + g) = q;
+      if (a.out) *(u32x4*)(a.out + g) = v;
+    } else {
+      *(u32x4*)(a.out + g) = q;
+    }
   }
 }
 
@@ -151,6 +272,7 @@ struct WgradArgs {
   const uint16_t* g;   // [P][cout]
   float* part;         // [nchunk][9][cin][cout]
   int h, w, cin, cout;
+  int up;              // in is at half resolution, read at (y/2, x/2)
   int64_t chunk;       // pixels per block, a multiple of 64
 };
 
@@ -179,14 +301,15 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
     const int64_t img = p / hw;
     const int rem = (int)(p - img * hw);
     const int y = rem / a.w, x = rem - (rem / a.w) * a.w;
-    uint4 xv[9];
+    u32x4 xv[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
       const int dy = t / 3 - 1, dx = t % 3 - 1;
-      const int64_t q = img * hw + (int64_t)wrap(y + dy, a.h) * a.w + wrap(x + dx, a.w);
-      xv[t] = *(const uint4*)(a.in + q * a.cin + ci0 + sc);
+      const int64_t q = img * (hw >> (2 * a.up)) + (int64_t)(wrap(y + dy, a.h) >> a.up) * (a.w >> a.up) +
+                        (wrap(x + dx, a.w) >> a.up);
+      xv[t] = *(const u32x4*)(a.in + q * a.cin + ci0 + sc);
     }
-    const uint4 gv = *(const uint4*)(a.g + p * a.cout + co0 + sc);
+    const u32x4 gv = *(const u32x4*)(a.g + p * a.cout + co0 + sc);
     __syncthreads();  // the previous slab has been consumed
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
@@ -200,11 +323,11 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
     __syncthreads();
 #pragma unroll
     for (int ks = 0; ks < 64; ks += 32) {
-      const bf16x8 bv = __builtin_bit_cast(bf16x8, *(const uint4*)&gs[sj + (lane & 15)][ks + 8 * (lane >> 4)]);
+      const bf16x8 bv = __builtin_bit_cast(bf16x8, *(const u32x4*)&gs[sj + (lane & 15)][ks + 8 * (lane >> 4)]);
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
         const bf16x8 av =
-            __builtin_bit_cast(bf16x8, *(const uint4*)&xs[t][si + (lane & 15)][ks + 8 * (lane >> 4)]);
+            __builtin_bit_cast(bf16x8, *(const u32x4*)&xs[t][si + (lane & 15)][ks + 8 * (lane >> 4)]);
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[t], 0, 0, 0);
       }
     }
@@ -252,7 +375,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* __restrict_
   const int64_t pbeg = (int64_t)blockIdx.x * chunk;
   if (lp < ppi) {
     for (int64_t p = pbeg + lp; p < pbeg + chunk; p += ppi) {
-      const uint4 u = *(const uint4*)(g + p * cout + 8 * v);
+      const u32x4 u = *(const u32x4*)(g + p * cout + 8 * v);
       const uint16_t* h = (const uint16_t*)&u;
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[e] += bf2f(h[e]);
@@ -273,31 +396,14 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* __restrict_
 // resampling and elementwise work on [P][C] bfloat16 (8 channels per thread)
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ void unpack8(uint4 v, float* f) {
-  const uint16_t* h = (const uint16_t*)&v;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = bf2f(h[e]);
-}
-__device__ __forceinline__ uint4 pack8(const float* f) {
-  uint4 v;
-  uint16_t* h = (uint16_t*)&v;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = f2bf(f[e]);
-  return v;
-}
-
-enum Ew { EW_POOL = 0, EW_UP = 1, EW_ADD = 2, EW_RELU_BWD = 3, EW_UP_ADJ = 4, EW_ADD_POOL_ADJ = 5 };
+enum Ew { EW_POOL = 0, EW_UP_ADJ = 1, EW_ADD_POOL_ADJ = 2 };
 
 // One thread per 8 channels of one output pixel.  Sizes (oh, ow) are the
 // output's; the coarse/fine partner is at half/double resolution.
-//   POOL        out[y][x] = mean of in[2y+a][2x+b]
-//   UP          out[y][x] = in[y/2][x/2]
-//   ADD         out = in + in2
-//   RELU_BWD    out = in * (in2 > 0)
-//   UP_ADJ      out[y][x] = sum of in[2y+a][2x+b]
-//   ADD_POOL_ADJ out[y][x] += in[y/2][x/2] / 4
-// (out may alias in: each thread reads its element before writing it)
-__global__ void ew_kernel(int op, const uint16_t* in, const uint16_t* in2, uint16_t* out, int64_t npix,
+//   POOL         out[y][x] = mean of in[2y+a][2x+b]
+//   UP_ADJ       out[y][x] = sum of in[2y+a][2x+b], where mask > 0
+//   ADD_POOL_ADJ out[y][x] = out[y][x] + in[y/2][x/2] / 4, where mask > 0
+__global__ void ew_kernel(int op, const uint16_t* in, const uint16_t* mask, uint16_t* out, int64_t npix,
                           int oh, int ow, int c) {
   const int c8 = c / 8;
   const int64_t total = npix * c8;
@@ -313,32 +419,29 @@ __global__ void ew_kernel(int op, const uint16_t* in, const uint16_t* in2, uint1
       const int ih = 2 * oh, iw = 2 * ow;
 #pragma unroll
       for (int e = 0; e < 8; ++e) f[e] = 0.f;
+#pragma unroll
       for (int a2 = 0; a2 < 2; ++a2)
+#pragma unroll
         for (int b2 = 0; b2 < 2; ++b2) {
           const int64_t q = (img * ih + 2 * y + a2) * iw + 2 * x + b2;
-          unpack8(*(const uint4*)(in + q * c + cc), g);
+          unpack8(*(const u32x4*)(in + q * c + cc), g);
 #pragma unroll
           for (int e = 0; e < 8; ++e) f[e] += g[e];
         }
       if (op == EW_POOL)
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] *= 0.25f;
-    } else if (op == EW_UP || op == EW_ADD_POOL_ADJ) {
+    } else {
       const int ih = oh / 2, iw = ow / 2;
       const int64_t q = (img * ih + y / 2) * iw + x / 2;
-      unpack8(*(const uint4*)(in + q * c + cc), f);
-      if (op == EW_ADD_POOL_ADJ) {
-        unpack8(*(const uint4*)(out + p * c + cc), g);
+      unpack8(*(const u32x4*)(in + q * c + cc), f);
+      unpack8(*(const u32x4*)(out + p * c + cc), g);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = g[e] + 0.25f * f[e];
-      }
-    } else {
-      unpack8(*(const uint4*)(in + p * c + cc), f);
-      unpack8(*(const uint4*)(in2 + p * c + cc), g);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) f[e] = (op == EW_ADD) ? f[e] + g[e] : (g[e] > 0.f ? f[e] : 0.f);
+      for (int e = 0; e < 8; ++e) f[e] = g[e] + 0.25f * f[e];
     }
-    *(uint4*)(out + p * c + cc) = pack8(f);
+    u32x4 v = pack8(f);
+    if (mask) v = mask8(v, *(const u32x4*)(mask + p * c + cc));
+    *(u32x4*)(out + p * c + cc) = v;
   }
 }
 
@@ -440,9 +543,9 @@ __global__ void features_kernel(const T* __restrict__ d, const T* __restrict__ n
       f[1] = (float)log((double)npix[p] / v2);
       f[2] = 1.f;
     }
-    uint4* row = (uint4*)(x + p * kPad);
+    u32x4* row = (u32x4*)(x + p * kPad);
     row[0] = pack8(f);
-    const uint4 z = {0u, 0u, 0u, 0u};
+    const u32x4 z = {0u, 0u, 0u, 0u};
     for (int k = 1; k < kPad / 8; ++k) row[k] = z;
     if (s && tgt) tgt[p] = (float)((double)s[p] / sg);
   }
@@ -453,9 +556,9 @@ __global__ void raw_features_kernel(const float* __restrict__ f4, int64_t P, uin
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < P;
        p += (int64_t)gridDim.x * blockDim.x) {
     float f[8] = {f4[4 * p], f4[4 * p + 1], f4[4 * p + 2], f4[4 * p + 3], 0.f, 0.f, 0.f, 0.f};
-    uint4* row = (uint4*)(x + p * kPad);
+    u32x4* row = (u32x4*)(x + p * kPad);
     row[0] = pack8(f);
-    const uint4 z = {0u, 0u, 0u, 0u};
+    const u32x4 z = {0u, 0u, 0u, 0u};
     for (int k = 1; k < kPad / 8; ++k) row[k] = z;
   }
 }
@@ -472,9 +575,9 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ y, 
     const float e = y[p] - t[p];
     s += (double)e * (double)e;
     float f[8] = {sc * e, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    uint4* row = (uint4*)(g + p * kPad);
+    u32x4* row = (u32x4*)(g + p * kPad);
     row[0] = pack8(f);
-    const uint4 z = {0u, 0u, 0u, 0u};
+    const u32x4 z = {0u, 0u, 0u, 0u};
     for (int k = 1; k < kPad / 8; ++k) row[k] = z;
   }
   sh[threadIdx.x] = s;
@@ -563,15 +666,57 @@ int grid_for(int64_t n, int block = 256, int cap = 8192) {
   return (int)(g < 1 ? 1 : (g > cap ? cap : g));
 }
 
-hipError_t conv(const uint16_t* in, const uint16_t* wt, const float* bias, uint16_t* out, float* out_f32,
-                int64_t P, int h, int w, int cin, int cout, bool flip, bool relu, hipStream_t st) {
-  ConvArgs a{in, wt, bias, out, out_f32, h, w, cin, cout, flip ? 1 : 0, relu ? 1 : 0, P};
-  const unsigned nb = (unsigned)((P + 127) / 128);
-  if (cout % 64 == 0)
-    hipLaunchKernelGGL(conv_kernel<64>, dim3(nb, cout / 64), dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL(conv_kernel<32>, dim3(nb, cout / 32), dim3(256), 0, st, a);
+// What a convolution does with its result (see ConvArgs).
+struct ConvOut {
+  uint16_t* out = nullptr;
+  uint16_t* out2 = nullptr;
+  const uint16_t* skip = nullptr;
+  const uint16_t* mask = nullptr;
+  float* f32 = nullptr;
+  bool relu = false;
+};
+
+template <int CIN, int COT>
+hipError_t conv_tiles(const ConvArgs& a, int64_t P, int ny, hipStream_t st) {
+  // tiles of 16 x 16 pixels (8 x 16 from 96 input channels on, whose border
+  // takes the LDS of two blocks otherwise), smaller ones where the image is
+  // smaller or the launch would leave CUs idle
+  if (a.w < 16) {
+    if (a.w != 8 || a.h % 8) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((conv_kernel<CIN, COT, 8, 1>), dim3((unsigned)(P / 64), ny), dim3(256), 0, st, a);
+  } else if (CIN <= 64 && a.h % 16 == 0 && P / 256 * ny >= 512) {
+    if constexpr (CIN <= 64)
+      hipLaunchKernelGGL((conv_kernel<CIN, COT, 16, 4>), dim3((unsigned)(P / 256), ny), dim3(256), 0, st, a);
+  } else if (a.h % 8 == 0) {
+    hipLaunchKernelGGL((conv_kernel<CIN, COT, 16, 2>), dim3((unsigned)(P / 128), ny), dim3(256), 0, st, a);
+  } else {
+    return hipErrorInvalidValue;
+  }
   return hipGetLastError();
+}
+
+template <int CIN>
+hipError_t conv_cin(const ConvArgs& a, int64_t P, hipStream_t st) {
+  if (!a.out && !a.out2) {  // channel 0 alone
+    if constexpr (CIN == kChan[0]) return conv_tiles<CIN, 16>(a, P, 1, st);
+    return hipErrorInvalidValue;
+  }
+  if (a.cout == 96) return conv_tiles<CIN, 96>(a, P, 1, st);
+  if (a.cout % 64 == 0) return conv_tiles<CIN, 64>(a, P, a.cout / 64, st);
+  return conv_tiles<CIN, 32>(a, P, a.cout / 32, st);
+}
+
+hipError_t conv(const uint16_t* in, const uint16_t* wt, const float* bias, const ConvOut& o, int64_t P, int h,
+                int w, int cin, int cout, bool flip, bool up, hipStream_t st) {
+  const ConvArgs a{in, wt, bias, o.out, o.out2, o.skip, o.mask, o.f32, h, w, cout, up ? 1 : 0, flip ? 1 : 0,
+                   o.relu ? 1 : 0};
+  switch (cin) {
+    case 32: return conv_cin<32>(a, P, st);
+    case 64: return conv_cin<64>(a, P, st);
+    case 96: return conv_cin<96>(a, P, st);
+    case 128: return conv_cin<128>(a, P, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // number of pixel chunks: the largest divisor of the 64-pixel slab count
@@ -595,9 +740,9 @@ int wgrad_chunks(int64_t P, int cin, int cout) {
 }
 
 hipError_t wgrad(const uint16_t* in, const uint16_t* g, float* part, float* dw, int64_t P, int h, int w,
-                 int cin, int cout, hipStream_t st) {
+                 int cin, int cout, bool up, hipStream_t st) {
   const int nch = wgrad_chunks(P, cin, cout);
-  WgradArgs a{in, g, part, h, w, cin, cout, P / nch};
+  WgradArgs a{in, g, part, h, w, cin, cout, up ? 1 : 0, P / nch};
   hipLaunchKernelGGL(wgrad_kernel, dim3(nch, (cin / 32) * (cout / 32)), dim3(256), 0, st, a);
   const int64_t n = (int64_t)9 * cin * cout;
   hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, part, nch, n, dw);
@@ -612,9 +757,9 @@ hipError_t bias_grad(const uint16_t* g, float* part, float* db, int64_t P, int c
   return hipGetLastError();
 }
 
-hipError_t ew(int op, const uint16_t* in, const uint16_t* in2, uint16_t* out, int64_t npix, int oh, int ow,
+hipError_t ew(int op, const uint16_t* in, const uint16_t* mask, uint16_t* out, int64_t npix, int oh, int ow,
               int c, hipStream_t st) {
-  hipLaunchKernelGGL(ew_kernel, dim3(grid_for(npix * (c / 8))), dim3(256), 0, st, op, in, in2, out, npix,
+  hipLaunchKernelGGL(ew_kernel, dim3(grid_for(npix * (c / 8))), dim3(256), 0, st, op, in, mask, out, npix,
                      oh, ow, c);
   return hipGetLastError();
 }
@@ -669,8 +814,7 @@ struct Net {
   uint16_t* ein[kLevels] = {};           // encoder input (l > 0: pooled)
   uint16_t* eh[kLevels] = {};
   uint16_t* ee[kLevels] = {};
-  uint16_t* da[kLevels] = {};            // decoder (l < L-1)
-  uint16_t* db[kLevels] = {};
+  uint16_t* db[kLevels] = {};            // decoder (l < L-1)
   uint16_t* dc[kLevels] = {};
   uint16_t* du[kLevels] = {};
   uint16_t* gen[kLevels] = {};           // gradient with respect to e_l
@@ -737,7 +881,6 @@ wf_status create_net(const wf_nn_shape* s, Net** out) {
     NA(n->eh[l], Pl * c * 2);
     NA(n->ee[l], Pl * c * 2);
     if (l < kLevels - 1) {
-      NA(n->da[l], Pl * kChan[l + 1] * 2);
       NA(n->db[l], Pl * c * 2);
       NA(n->dc[l], Pl * c * 2);
       NA(n->du[l], Pl * c * 2);
@@ -775,10 +918,17 @@ hipError_t pack_all(Net* n, hipStream_t st) {
   return hipGetLastError();
 }
 
-// forward pass of nb maps from n->x into n->yf
-wf_status forward(Net* n, int nb, hipStream_t st) {
+// forward pass of nb maps from n->x into n->yf; keep: every activation that the
+// backward pass needs is stored (the decoder's b_l among them)
+wf_status forward(Net* n, int nb, bool keep, hipStream_t st) {
   const int64_t P0 = (int64_t)nb * n->h * n->w;
   int k = 0;
+  auto relu = [](uint16_t* out) {
+    ConvOut o;
+    o.out = out;
+    o.relu = true;
+    return o;
+  };
   for (int l = 0; l < kLevels; ++l) {
     const int64_t Pl = P0 >> (2 * l);
     const int hl = n->h >> l, wl = n->w >> l;
@@ -786,8 +936,8 @@ wf_status forward(Net* n, int nb, hipStream_t st) {
     if (l > 0) NN_TRY(ew(EW_POOL, n->ee[l - 1], nullptr, n->ein[l], Pl, hl, wl, cin, st));
     const Layer& a = n->L[k];
     const Layer& b = n->L[k + 1];
-    NN_TRY(conv(n->ein[l], a.wt, n->prm + a.b_off, n->eh[l], nullptr, Pl, hl, wl, a.ci, a.co, false, true, st));
-    NN_TRY(conv(n->eh[l], b.wt, n->prm + b.b_off, n->ee[l], nullptr, Pl, hl, wl, b.ci, b.co, false, true, st));
+    NN_TRY(conv(n->ein[l], a.wt, n->prm + a.b_off, relu(n->eh[l]), Pl, hl, wl, a.ci, a.co, false, false, st));
+    NN_TRY(conv(n->eh[l], b.wt, n->prm + b.b_off, relu(n->ee[l]), Pl, hl, wl, b.ci, b.co, false, false, st));
     k += 2;
   }
   const uint16_t* u = n->ee[kLevels - 1];
@@ -796,76 +946,84 @@ wf_status forward(Net* n, int nb, hipStream_t st) {
     const int hl = n->h >> l, wl = n->w >> l;
     const Layer& a = n->L[k];
     const Layer& b = n->L[k + 1];
-    NN_TRY(ew(EW_UP, u, nullptr, n->da[l], Pl, hl, wl, kChan[l + 1], st));
-    NN_TRY(conv(n->da[l], a.wt, n->prm + a.b_off, n->db[l], nullptr, Pl, hl, wl, a.ci, a.co, false, true, st));
-    NN_TRY(ew(EW_ADD, n->db[l], n->ee[l], n->dc[l], Pl, hl, wl, kChan[l], st));
-    NN_TRY(conv(n->dc[l], b.wt, n->prm + b.b_off, n->du[l], nullptr, Pl, hl, wl, b.ci, b.co, false, true, st));
+    // b_l = R(conv(up(u))), c_l = b_l + e_l
+    ConvOut o = relu(keep ? n->db[l] : nullptr);
+    o.out2 = n->dc[l];
+    o.skip = n->ee[l];
+    NN_TRY(conv(u, a.wt, n->prm + a.b_off, o, Pl, hl, wl, a.ci, a.co, false, true, st));
+    NN_TRY(conv(n->dc[l], b.wt, n->prm + b.b_off, relu(n->du[l]), Pl, hl, wl, b.ci, b.co, false, false, st));
     u = n->du[l];
     k += 2;
   }
-  const Layer& o = n->L[k];
-  NN_TRY(conv(u, o.wt, n->prm + o.b_off, nullptr, n->yf, P0, n->h, n->w, o.ci, o.co, false, false, st));
+  const Layer& y = n->L[k];
+  ConvOut o;
+  o.f32 = n->yf;
+  NN_TRY(conv(u, y.wt, n->prm + y.b_off, o, P0, n->h, n->w, y.ci, y.co, false, false, st));
   return WF_OK;
 }
 
-// loss against n->tgt and the gradient of every parameter into n->grad
+// loss against n->tgt and the gradient of every parameter into n->grad.  A
+// gradient is masked by its layer's ReLU where it is formed: in the adjoint
+// convolution that makes it, or in the resampling's adjoint.
 wf_status backward(Net* n, int nb, hipStream_t st) {
   const int64_t P0 = (int64_t)nb * n->h * n->w;
   const int nlp = grid_for(P0, 256, 1024);
   hipLaunchKernelGGL(loss_kernel, dim3(nlp), dim3(256), 0, st, n->yf, n->tgt, P0, n->gy, n->lpart);
   hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, n->lpart, nlp, P0, n->loss);
   NN_TRY(hipGetLastError());
+  // adjoint of layer ly in its input, masked where the activation is not positive
+  auto adjoint = [&](const Layer& ly, const uint16_t* g, uint16_t* out, uint16_t* masked,
+                     const uint16_t* act, int64_t P, int h, int w) {
+    ConvOut o;
+    o.out = out ? out : masked;
+    o.out2 = out ? masked : nullptr;
+    o.mask = act;
+    return conv(g, ly.w_orig, nullptr, o, P, h, w, ly.co, ly.ci, true, false, st);
+  };
   int k = kLayers - 1;
+  uint16_t* gu = n->g1[0];  // gradient of u_l's pre-activation
   {
     const Layer& o = n->L[k];
-    NN_TRY(wgrad(n->du[0], n->gy, n->part, n->grad + o.w_off, P0, n->h, n->w, o.ci, o.co, st));
+    NN_TRY(wgrad(n->du[0], n->gy, n->part, n->grad + o.w_off, P0, n->h, n->w, o.ci, o.co, false, st));
     NN_TRY(bias_grad(n->gy, n->part, n->grad + o.b_off, P0, o.co, st));
-    NN_TRY(conv(n->gy, o.w_orig, nullptr, n->g1[0], nullptr, P0, n->h, n->w, o.co, o.ci, true, false, st));
+    NN_TRY(adjoint(o, n->gy, nullptr, gu, n->du[0], P0, n->h, n->w));
   }
-  // g1[0] holds the gradient with respect to u_0
-  uint16_t* gu = n->g1[0];
   k -= 1;
   for (int l = 0; l < kLevels - 1; ++l) {
     const int64_t Pl = P0 >> (2 * l);
     const int hl = n->h >> l, wl = n->w >> l;
     const Layer& b = n->L[k];      // second convolution of decoder level l
     const Layer& a = n->L[k - 1];  // first one
-    const int c = kChan[l];
-    NN_TRY(ew(EW_RELU_BWD, gu, n->du[l], gu, Pl, hl, wl, c, st));
-    NN_TRY(wgrad(n->dc[l], gu, n->part, n->grad + b.w_off, Pl, hl, wl, b.ci, b.co, st));
+    NN_TRY(wgrad(n->dc[l], gu, n->part, n->grad + b.w_off, Pl, hl, wl, b.ci, b.co, false, st));
     NN_TRY(bias_grad(gu, n->part, n->grad + b.b_off, Pl, b.co, st));
-    // gradient with respect to c_l = b_l + e_l goes to the skip and to b_l
-    NN_TRY(conv(gu, b.w_orig, nullptr, n->gen[l], nullptr, Pl, hl, wl, b.co, b.ci, true, false, st));
-    uint16_t* gb = (gu == n->g1[l]) ? n->g2[l] : n->g1[l];
-    NN_TRY(ew(EW_RELU_BWD, n->gen[l], n->db[l], gb, Pl, hl, wl, c, st));
-    NN_TRY(wgrad(n->da[l], gb, n->part, n->grad + a.w_off, Pl, hl, wl, a.ci, a.co, st));
+    // gradient with respect to c_l = b_l + e_l: to the skip, and to b_l
+    uint16_t* gb = n->g2[l];
+    NN_TRY(adjoint(b, gu, n->gen[l], gb, n->db[l], Pl, hl, wl));
+    NN_TRY(wgrad(l + 1 < kLevels - 1 ? n->du[l + 1] : n->ee[l + 1], gb, n->part, n->grad + a.w_off, Pl, hl, wl,
+                 a.ci, a.co, true, st));
     NN_TRY(bias_grad(gb, n->part, n->grad + a.b_off, Pl, a.co, st));
-    uint16_t* ga = (gb == n->g1[l]) ? n->g2[l] : n->g1[l];
-    NN_TRY(conv(gb, a.w_orig, nullptr, ga, nullptr, Pl, hl, wl, a.co, a.ci, true, false, st));
+    uint16_t* ga = n->g1[l];
+    NN_TRY(adjoint(a, gb, ga, nullptr, nullptr, Pl, hl, wl));
     // adjoint of the upsampling: gradient with respect to u_{l+1}
-    NN_TRY(ew(EW_UP_ADJ, ga, nullptr, n->g1[l + 1], Pl >> 2, hl / 2, wl / 2, kChan[l + 1], st));
-    gu = n->g1[l + 1];
+    const bool top = l + 1 == kLevels - 1;
+    gu = top ? n->gen[l + 1] : n->g1[l + 1];
+    NN_TRY(ew(EW_UP_ADJ, ga, top ? n->ee[l + 1] : n->du[l + 1], gu, Pl >> 2, hl / 2, wl / 2, kChan[l + 1], st));
     k -= 2;
   }
-  // gu: gradient with respect to e_{L-1}
-  NN_TRY(hipMemcpyAsync(n->gen[kLevels - 1], gu, (size_t)(P0 >> (2 * (kLevels - 1))) * kChan[kLevels - 1] * 2,
-                        hipMemcpyDeviceToDevice, st));
+  // gen[l]: gradient of e_l's pre-activation
   for (int l = kLevels - 1; l >= 0; --l) {
     const int64_t Pl = P0 >> (2 * l);
     const int hl = n->h >> l, wl = n->w >> l;
     const Layer& a = n->L[2 * l];
     const Layer& b = n->L[2 * l + 1];
-    const int c = kChan[l];
-    NN_TRY(ew(EW_RELU_BWD, n->gen[l], n->ee[l], n->gen[l], Pl, hl, wl, c, st));
-    NN_TRY(wgrad(n->eh[l], n->gen[l], n->part, n->grad + b.w_off, Pl, hl, wl, b.ci, b.co, st));
+    NN_TRY(wgrad(n->eh[l], n->gen[l], n->part, n->grad + b.w_off, Pl, hl, wl, b.ci, b.co, false, st));
     NN_TRY(bias_grad(n->gen[l], n->part, n->grad + b.b_off, Pl, b.co, st));
-    NN_TRY(conv(n->gen[l], b.w_orig, nullptr, n->g1[l], nullptr, Pl, hl, wl, b.co, b.ci, true, false, st));
-    NN_TRY(ew(EW_RELU_BWD, n->g1[l], n->eh[l], n->g1[l], Pl, hl, wl, c, st));
-    NN_TRY(wgrad(n->ein[l], n->g1[l], n->part, n->grad + a.w_off, Pl, hl, wl, a.ci, a.co, st));
+    NN_TRY(adjoint(b, n->gen[l], nullptr, n->g1[l], n->eh[l], Pl, hl, wl));
+    NN_TRY(wgrad(n->ein[l], n->g1[l], n->part, n->grad + a.w_off, Pl, hl, wl, a.ci, a.co, false, st));
     NN_TRY(bias_grad(n->g1[l], n->part, n->grad + a.b_off, Pl, a.co, st));
     if (l > 0) {
-      NN_TRY(conv(n->g1[l], a.w_orig, nullptr, n->g2[l], nullptr, Pl, hl, wl, a.co, a.ci, true, false, st));
-      NN_TRY(ew(EW_ADD_POOL_ADJ, n->g2[l], nullptr, n->gen[l - 1], Pl << 2, hl * 2, wl * 2, kChan[l - 1], st));
+      NN_TRY(adjoint(a, n->g1[l], n->g2[l], nullptr, nullptr, Pl, hl, wl));
+      NN_TRY(ew(EW_ADD_POOL_ADJ, n->g2[l], n->ee[l - 1], n->gen[l - 1], Pl << 2, hl * 2, wl * 2, kChan[l - 1], st));
     }
   }
   return WF_OK;
@@ -966,7 +1124,7 @@ wf_status wf_nn_predict(void* net, int32_t nb, const void* d, const void* n_pix,
   wf_status st = n->prec == WF_F64 ? prepare<double>(n, nb, d, n_pix, mask, nullptr, stream)
                                    : prepare<float>(n, nb, d, n_pix, mask, nullptr, stream);
   if (st != WF_OK) return st;
-  st = forward(n, nb, stream);
+  st = forward(n, nb, false, stream);
   if (st != WF_OK) return st;
   if (n->prec == WF_F64)
     hipLaunchKernelGGL(scale_out_kernel<double>, dim3(grid_for(P0)), dim3(256), 0, stream, n->yf, n->sig2, hw,
@@ -987,7 +1145,7 @@ wf_status wf_nn_train_step(void* net, int32_t nb, const void* d, const void* n_p
   wf_status st = n->prec == WF_F64 ? prepare<double>(n, nb, d, n_pix, mask, s_target, stream)
                                    : prepare<float>(n, nb, d, n_pix, mask, s_target, stream);
   if (st != WF_OK) return st;
-  if ((st = forward(n, nb, stream)) != WF_OK) return st;
+  if ((st = forward(n, nb, true, stream)) != WF_OK) return st;
   if ((st = backward(n, nb, stream)) != WF_OK) return st;
   if ((st = adam(n, lr, stream)) != WF_OK) return st;
   return read_loss(n, loss, stream);
@@ -999,7 +1157,7 @@ wf_status wf_nn_forward_features(void* net, int32_t nb, const float* x, float* y
   const int64_t P0 = (int64_t)nb * n->h * n->w;
   hipLaunchKernelGGL(raw_features_kernel, dim3(grid_for(P0)), dim3(256), 0, stream, x, P0, n->x);
   NN_TRY(hipGetLastError());
-  wf_status st = forward(n, nb, stream);
+  wf_status st = forward(n, nb, false, stream);
   if (st != WF_OK) return st;
   NN_TRY(hipMemcpyAsync(y, n->yf, P0 * 4, hipMemcpyDeviceToDevice, stream));
   NN_TRY(hipStreamSynchronize(stream));
@@ -1014,7 +1172,7 @@ wf_status wf_nn_gradient_features(void* net, int32_t nb, const float* x, const f
   hipLaunchKernelGGL(raw_features_kernel, dim3(grid_for(P0)), dim3(256), 0, stream, x, P0, n->x);
   NN_TRY(hipGetLastError());
   NN_TRY(hipMemcpyAsync(n->tgt, target, P0 * 4, hipMemcpyDeviceToDevice, stream));
-  wf_status st = forward(n, nb, stream);
+  wf_status st = forward(n, nb, true, stream);
   if (st != WF_OK) return st;
   if ((st = backward(n, nb, stream)) != WF_OK) return st;
   NN_TRY(hipMemcpyAsync(grad, n->grad, n->nparam * 4, hipMemcpyDeviceToDevice, stream));
@@ -1033,7 +1191,7 @@ wf_status wf_nn_conv3x3(int32_t mode, int32_t nb, int32_t h, int32_t w, int32_t 
     if (!g) return WF_EINVAL;
     float* part = nullptr;
     NN_TRY(hipMalloc((void**)&part, (size_t)wgrad_chunks(P, ci, co) * 9 * ci * co * 4));
-    hipError_t e = wgrad(in, g, part, (float*)out, P, h, w, ci, co, stream);
+    hipError_t e = wgrad(in, g, part, (float*)out, P, h, w, ci, co, false, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     (void)hipFree(part);
     return from_hip(e);
@@ -1041,7 +1199,9 @@ wf_status wf_nn_conv3x3(int32_t mode, int32_t nb, int32_t h, int32_t w, int32_t 
   if (!wt) return WF_EINVAL;
   if (mode == 2) {
     // input adjoint: the [9][ci][co] weights are already [tap][out = ci][reduction = co]
-    NN_TRY(conv(in, wt, nullptr, (uint16_t*)out, nullptr, P, h, w, co, ci, true, false, stream));
+    ConvOut o;
+    o.out = (uint16_t*)out;
+    NN_TRY(conv(in, wt, nullptr, o, P, h, w, co, ci, true, false, stream));
     NN_TRY(hipStreamSynchronize(stream));
     return WF_OK;
   }
@@ -1057,7 +1217,10 @@ wf_status wf_nn_conv3x3(int32_t mode, int32_t nb, int32_t h, int32_t w, int32_t 
         for (int c = 0; c < co; ++c) ht[((size_t)t * co + c) * ci + a] = hw_[((size_t)t * ci + a) * co + c];
     e = hipMemcpyAsync(tmp, ht.data(), ht.size() * 2, hipMemcpyHostToDevice, stream);
   }
-  if (e == hipSuccess) e = conv(in, tmp, b, (uint16_t*)out, nullptr, P, h, w, ci, co, false, mode == 1, stream);
+  ConvOut o;
+  o.out = (uint16_t*)out;
+  o.relu = mode == 1;
+  if (e == hipSuccess) e = conv(in, tmp, b, o, P, h, w, ci, co, false, false, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   (void)hipFree(tmp);
   return from_hip(e);
