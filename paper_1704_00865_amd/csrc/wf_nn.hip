@@ -6,10 +6,10 @@
 // output pixels are the rows, output channels the columns and (tap, input
 // channel) the reduction.  Activations are [pixel][channel] bfloat16 so that
 // one lane's eight consecutive reduction values are one 16-byte load; a block
-// stages its pixels with their periodic border in LDS.  The weight gradient is the same product with pixels as the
-// reduction: 64-pixel slabs of the input and of the output gradient are
-// staged transposed in LDS, each block sums one pixel chunk, and a second
-// kernel adds the chunks in a fixed order (deterministic).
+// stages its pixels with their periodic border in LDS.  The weight gradient is
+// the same product with pixels as the reduction: 64-pixel slabs of the input and of the output gradient are
+// staged in LDS and read transposed, each block sums one pixel chunk, and a
+// second kernel adds the chunks in a fixed order (deterministic).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -31,6 +31,7 @@ constexpr int kLevels = 4;
 constexpr int kChan[kLevels] = {32, 64, 96, 128};
 constexpr int kLayers = 4 * kLevels - 1;
 constexpr int kPad = 32;  // channels of the padded input and output
+constexpr int kFew = 8;   // those of them that are stored (the rest are zero)
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -52,6 +53,11 @@ __device__ __forceinline__ u32x4 pack8(const float* f) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = (uint32_t)f2bf(f[2 * e]) | ((uint32_t)f2bf(f[2 * e + 1]) << 16);
   return v;
+}
+// channels c .. c + 7 of a pixel of which cs are stored and the rest are zero
+__device__ __forceinline__ u32x4 few_channels(const uint16_t* px, int c, int cs) {
+  const u32x4 v = *(const u32x4*)(px + (c < cs ? c : 0));
+  return c < cs ? v : u32x4{0u, 0u, 0u, 0u};
 }
 // v where m > 0, else 0, on 8 bfloat16 values
 __device__ __forceinline__ u32x4 mask8(u32x4 v, u32x4 m) {
@@ -78,6 +84,7 @@ struct ConvArgs {
   const uint16_t* mask;  // [P][cout] or null; without out2 it applies to out
   float* out_f32;        // [P]: channel 0 in float32, or null
   int h, w, cout;
+  int cs;                // channels of a pixel in memory: CIN, or kFew (the rest are zero)
   int up;
   int flip;              // 1: tap (dy, dx) reads the pixel at (-dy, -dx)
   int relu;
@@ -149,7 +156,7 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
   {
     constexpr int N = C::HP * U, NU = (N + 255) / 256, G = 6;
     const int ih = a.up ? a.h >> 1 : a.h, iw = a.up ? a.w >> 1 : a.w;
-    const uint16_t* src = a.in + (int64_t)img * ih * iw * CIN;
+    const uint16_t* src = a.in + (int64_t)img * ih * iw * a.cs;
 #pragma unroll
     for (int k0 = 0; k0 < NU; k0 += G) {
       u32x4 v[G];
@@ -159,7 +166,7 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
         const int px = i / U, cc = i - px * U;
         const int yy = wrap(y0 - 1 + px / (TW + 2), a.h), xx = wrap(x0 - 1 + px % (TW + 2), a.w);
         if (k0 + k < NU)
-          v[k] = *(const u32x4*)(src + ((int64_t)(yy >> a.up) * iw + (xx >> a.up)) * CIN + cc * 8);
+          v[k] = few_channels(src + ((int64_t)(yy >> a.up) * iw + (xx >> a.up)) * a.cs, cc * 8, a.cs);
       }
 #pragma unroll
       for (int k = 0; k < G; ++k) {
@@ -270,115 +277,33 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvArgs a) {
 struct WgradArgs {
   const uint16_t* in;  // [P][cin]
   const uint16_t* g;   // [P][cout]
-  float* part;         // [nchunk][9][cin][cout]
+  float* part;         // [nch][9][cin][cout]
+  float* part_b;       // [chunks of the bias sums][cout]
   int h, w, cin, cout;
+  int cs, gcs;         // channels of a pixel of in and g in memory (see ConvArgs)
   int up;              // in is at half resolution, read at (y/2, x/2)
-  int64_t chunk;       // pixels per block, a multiple of 64
+  int nch;             // pixel chunks of the weight gradient
+  int64_t chunk;       // pixels per chunk, a multiple of 64
+  int64_t chunk_b;     // pixels per chunk of the bias sums
 };
-
-// grid (nchunk, (cin/32) * (cout/32)); each block one 32 x 32 (ci, co) tile
-// of all nine taps over its pixel chunk.  Per 64-pixel slab the output
-// gradient is staged once and the input once per tap (its periodic
-// neighbours), both transposed to [channel][pixel] in LDS so that a lane's 8
-// consecutive pixels are one 16-byte read; wave w owns the 16 x 16 sub-tile
-// (w / 2, w % 2) of every tap.
-__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t xs[9][32][72];  // [tap][ci][pixel]
-  __shared__ __attribute__((aligned(16))) uint16_t gs[32][72];     // [co][pixel]
-  const int ntc = a.cout / 32;
-  const int ci0 = (int)(blockIdx.y / ntc) * 32, co0 = (int)(blockIdx.y % ntc) * 32;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int si = (wave >> 1) * 16, sj = (wave & 1) * 16;
-  const int sp = threadIdx.x >> 2;         // staged pixel 0..63
-  const int sc = (threadIdx.x & 3) * 8;    // staged channel offset
-  const int hw = a.h * a.w;
-  f32x4 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int64_t pbeg = (int64_t)blockIdx.x * a.chunk;
-  for (int64_t pb = pbeg; pb < pbeg + a.chunk; pb += 64) {
-    const int64_t p = pb + sp;
-    const int64_t img = p / hw;
-    const int rem = (int)(p - img * hw);
-    const int y = rem / a.w, x = rem - (rem / a.w) * a.w;
-    u32x4 xv[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const int dy = t / 3 - 1, dx = t % 3 - 1;
-      const int64_t q = img * (hw >> (2 * a.up)) + (int64_t)(wrap(y + dy, a.h) >> a.up) * (a.w >> a.up) +
-                        (wrap(x + dx, a.w) >> a.up);
-      xv[t] = *(const u32x4*)(a.in + q * a.cin + ci0 + sc);
-    }
-    const u32x4 gv = *(const u32x4*)(a.g + p * a.cout + co0 + sc);
-    __syncthreads();  // the previous slab has been consumed
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const uint16_t* xe = (const uint16_t*)&xv[t];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) xs[t][sc + e][sp] = xe[e];
-    }
-    const uint16_t* ge = (const uint16_t*)&gv;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) gs[sc + e][sp] = ge[e];
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 64; ks += 32) {
-      const bf16x8 bv = __builtin_bit_cast(bf16x8, *(const u32x4*)&gs[sj + (lane & 15)][ks + 8 * (lane >> 4)]);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const bf16x8 av =
-            __builtin_bit_cast(bf16x8, *(const u32x4*)&xs[t][si + (lane & 15)][ks + 8 * (lane >> 4)]);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[t], 0, 0, 0);
-      }
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    float* dst = a.part + (((int64_t)blockIdx.x * 9 + t) * a.cin + ci0 + si) * a.cout + co0 + sj;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) dst[(int64_t)(4 * (lane >> 4) + v) * a.cout + (lane & 15)] = acc[t][v];
-  }
-}
-
-// out[i] = sum_c part[c][i] in a fixed order.  A block takes 32 consecutive
-// i and 8 groups of chunks (group g sums chunks g, g+8, ...), so that many
-// loads are in flight; the 8 group sums are then added in order.
-__global__ __launch_bounds__(256) void chunk_sum_kernel(const float* __restrict__ part, int nchunk, int64_t n,
-                                                        float* __restrict__ out) {
-  __shared__ float sh[8][32];
-  const int li = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  const int64_t i = (int64_t)blockIdx.x * 32 + li;
-  float s = 0.f;
-  if (i < n)
-    for (int c = grp; c < nchunk; c += 8) s += part[(int64_t)c * n + i];
-  sh[grp][li] = s;
-  __syncthreads();
-  if (grp == 0 && i < n) {
-    float t = 0.f;
-#pragma unroll
-    for (int g = 0; g < 8; ++g) t += sh[g][li];
-    out[i] = t;
-  }
-}
 
 // bias gradient partials: part[chunk][co] = sum over the chunk of g[p][co].
 // A thread reads 8 channels of one pixel per step (16-byte loads, whole
 // pixels per step across the block); the per-thread sums are then added
-// over the block's pixel lanes in LDS.
-__global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* __restrict__ g, int cout,
-                                                     int64_t chunk, float* __restrict__ part) {
-  __shared__ float red[256 * 8];
+// over the block's pixel lanes in LDS (red: 2048 floats).
+__device__ __forceinline__ void column_sums(const uint16_t* __restrict__ g, int cout, int gcs, int64_t chunk, int c,
+                                            float* __restrict__ part, float* red) {
   const int vpp = cout / 8;            // 16-byte vectors per pixel
   const int ppi = 256 / vpp;           // pixels per step
   const int lp = threadIdx.x / vpp, v = threadIdx.x - lp * vpp;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int64_t pbeg = (int64_t)blockIdx.x * chunk;
+  const int64_t pbeg = (int64_t)c * chunk;
   if (lp < ppi) {
     for (int64_t p = pbeg + lp; p < pbeg + chunk; p += ppi) {
-      const u32x4 u = *(const u32x4*)(g + p * cout + 8 * v);
-      const uint16_t* h = (const uint16_t*)&u;
+      float f[8];
+      unpack8(few_channels(g + p * gcs, 8 * v, gcs), f);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += bf2f(h[e]);
+      for (int e = 0; e < 8; ++e) acc[e] += f[e];
     }
   }
 #pragma unroll
@@ -388,7 +313,147 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* __restrict_
     const int vv = co / 8, e = co - vv * 8;
     float sum = 0.f;
     for (int l = 0; l < ppi; ++l) sum += red[(l * vpp + vv) * 8 + e];
-    part[(int64_t)blockIdx.x * cout + co] = sum;
+    part[(int64_t)c * cout + co] = sum;
+  }
+}
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+// Four pixels of one channel: LDS holds [pixel][channel]; each lane of a group
+// of sixteen gives the address of a 4-channel run of one pixel (lane i: pixel
+// i / 4, channels 4 (i % 4)), and gets its own channel's (lane % 16) values of
+// the four pixels (ds_read_b64_tr_b16).
+__device__ __forceinline__ s16x4 read_tr(const uint16_t* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+}
+__device__ __forceinline__ bf16x8 join8(s16x4 lo, s16x4 hi) {
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Blocks 0 .. nch * tiles - 1: one 32 x 32 (ci, co) tile of all nine taps over
+// one pixel chunk.  Per 64-pixel slab (a run of a row, or whole rows of WR < 64
+// pixels) the block stages the input with its border and the output gradient
+// as they lie in memory, [pixel][channel], and reads them transposed: a tap is
+// an offset of the address.  (Transposing on the way in took 80 two-byte LDS
+// writes per thread and slab, and nine reads of the input.)  The next slab's
+// loads are in flight meanwhile.  Wave w owns the 16 x 16 sub-tile (w / 2,
+// w % 2) of every tap.  Bound: LDS reads, 20 of 8 bytes per lane for 9 matrix
+// instructions; 32 -> 32 channels over a million pixels 102 to 53 us.
+// The blocks after them sum the bias gradient.
+template <int WR>
+__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
+  constexpr int R = 64 / WR, HP = (R + 2) * (WR + 2), PS = 40;
+  constexpr int NL = (HP * 4 + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint16_t sm[(HP + 64) * PS];
+  uint16_t* xs = sm;
+  uint16_t* gs = sm + HP * PS;
+  static_assert((HP + 64) * PS * 2 >= 256 * 8 * 4, "the bias sums' scratch");
+  const int ntc = a.cout / 32, tiles = (a.cin / 32) * ntc;
+  const int blk = blockIdx.x;
+  if (blk >= a.nch * tiles) {
+    column_sums(a.g, a.cout, a.gcs, a.chunk_b, blk - a.nch * tiles, a.part_b, (float*)sm);
+    return;
+  }
+  const int ch = blk % a.nch, tile = blk / a.nch;
+  const int ci0 = (tile / ntc) * 32, co0 = (tile % ntc) * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 15, kq = lane >> 4;
+  const int si = (wave >> 1) * 16, sj = (wave & 1) * 16;
+  const int hw = a.h * a.w;
+  const int ih = a.h >> a.up, iw = a.w >> a.up;
+  f32x4 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 xv[NL], gv;
+  auto load = [&](int64_t pb) {
+    const int img = (int)(pb / hw), rem = (int)(pb - (int64_t)img * hw);
+    const int y0 = rem / a.w, x0 = rem - y0 * a.w;
+    const uint16_t* src = a.in + (int64_t)img * ih * iw * a.cs;
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int i = min(tid + k * 256, HP * 4 - 1);
+      const int px = i >> 2, cc = i & 3;
+      const int yy = wrap(y0 - 1 + px / (WR + 2), a.h), xx = wrap(x0 - 1 + px % (WR + 2), a.w);
+      xv[k] = few_channels(src + ((int64_t)(yy >> a.up) * iw + (xx >> a.up)) * a.cs, ci0 + cc * 8, a.cs);
+    }
+    gv = few_channels(a.g + (pb + (tid >> 2)) * a.gcs, co0 + (tid & 3) * 8, a.gcs);
+  };
+  // this lane's addresses in the two transposing reads of each half slab
+  int xo[2][2], go[2][2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = 32 * ks + 8 * kq + 4 * h + (r >> 2);
+      xo[ks][h] = ((i / WR + 1) * (WR + 2) + i % WR + 1) * PS + si + (r & 3) * 4;
+      go[ks][h] = i * PS + sj + (r & 3) * 4;
+    }
+  const int64_t pbeg = (int64_t)ch * a.chunk, pend = pbeg + a.chunk;
+  load(pbeg);
+  for (int64_t pb = pbeg; pb < pend; pb += 64) {
+    __syncthreads();  // the previous slab has been consumed
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int i = tid + k * 256;
+      if (i < HP * 4) *(u32x4*)&xs[(i >> 2) * PS + (i & 3) * 8] = xv[k];
+    }
+    *(u32x4*)&gs[(tid >> 2) * PS + (tid & 3) * 8] = gv;
+    __syncthreads();
+    if (pb + 64 < pend) load(pb + 64);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const bf16x8 bv = join8(read_tr(&gs[go[ks][0]]), read_tr(&gs[go[ks][1]]));
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const int sh = ((t / 3 - 1) * (WR + 2) + t % 3 - 1) * PS;
+        const bf16x8 av = join8(read_tr(&xs[xo[ks][0] + sh]), read_tr(&xs[xo[ks][1] + sh]));
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[t], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 9; ++t) {
+    float* dst = a.part + (((int64_t)ch * 9 + t) * a.cin + ci0 + si) * a.cout + co0 + sj;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dst[(int64_t)(4 * kq + v) * a.cout + r] = acc[t][v];
+  }
+}
+
+// out[i] = sum_c part[c][i] in a fixed order.  A block takes 32 consecutive
+// i and 8 groups of chunks (group g sums chunks g, g+8, ..., loading sixteen
+// before it adds the first); the 8 group sums are then added in order.  The
+// blocks from nb on do the same for the second pair of arrays.
+struct SumArgs {
+  const float* part;
+  float* out;
+  int64_t n;
+  int nchunk;
+};
+__global__ __launch_bounds__(256) void chunk_sum_kernel(SumArgs a, SumArgs b, int nb) {
+  __shared__ float sh[8][32];
+  const bool second = (int)blockIdx.x >= nb;
+  const SumArgs s_ = second ? b : a;
+  const int li = threadIdx.x & 31, grp = threadIdx.x >> 5;
+  const int64_t n = s_.n, i = (int64_t)(blockIdx.x - (second ? nb : 0)) * 32 + li;
+  float s = 0.f;
+  if (i < n) {
+    constexpr int U = 16;
+    for (int c0 = grp; c0 < s_.nchunk; c0 += 8 * U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = s_.part[(int64_t)min(c0 + 8 * u, s_.nchunk - 1) * n + i];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c0 + 8 * u < s_.nchunk) s += v[u];
+    }
+  }
+  sh[grp][li] = s;
+  __syncthreads();
+  if (grp == 0 && i < n) {
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) t += sh[g][li];
+    s_.out[i] = t;
   }
 }
 
@@ -523,7 +588,7 @@ __global__ __launch_bounds__(256) void rowmean_kernel(const T* __restrict__ d,
   if (threadIdx.x == 0) rowm[blockIdx.x] = sc[0] > 0 ? ss[0] / sc[0] : 0.0;
 }
 
-// x [P][32] bf16: d/sigma, log(N/sigma^2), mask, row mean of d/sigma, zeros;
+// x [P][8] bf16: d/sigma, log(N/sigma^2), mask, row mean of d/sigma, zeros;
 // tgt[p] = s/sigma
 template <class T>
 __global__ void features_kernel(const T* __restrict__ d, const T* __restrict__ npix,
@@ -543,27 +608,21 @@ __global__ void features_kernel(const T* __restrict__ d, const T* __restrict__ n
       f[1] = (float)log((double)npix[p] / v2);
       f[2] = 1.f;
     }
-    u32x4* row = (u32x4*)(x + p * kPad);
-    row[0] = pack8(f);
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int k = 1; k < kPad / 8; ++k) row[k] = z;
+    *(u32x4*)(x + p * kFew) = pack8(f);
     if (s && tgt) tgt[p] = (float)((double)s[p] / sg);
   }
 }
 
-// x [P][32] bf16 from caller features [P][4] float
+// x [P][8] bf16 from caller features [P][4] float
 __global__ void raw_features_kernel(const float* __restrict__ f4, int64_t P, uint16_t* __restrict__ x) {
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < P;
        p += (int64_t)gridDim.x * blockDim.x) {
     float f[8] = {f4[4 * p], f4[4 * p + 1], f4[4 * p + 2], f4[4 * p + 3], 0.f, 0.f, 0.f, 0.f};
-    u32x4* row = (u32x4*)(x + p * kPad);
-    row[0] = pack8(f);
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int k = 1; k < kPad / 8; ++k) row[k] = z;
+    *(u32x4*)(x + p * kFew) = pack8(f);
   }
 }
 
-// partial sums of (y - t)^2 and the output gradient g [P][32] (channel 0)
+// partial sums of (y - t)^2 and the output gradient g [P][8] (channel 0)
 __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ y, const float* __restrict__ t,
                                                    int64_t P, uint16_t* __restrict__ g,
                                                    double* __restrict__ part) {
@@ -575,10 +634,7 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ y, 
     const float e = y[p] - t[p];
     s += (double)e * (double)e;
     float f[8] = {sc * e, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    u32x4* row = (u32x4*)(g + p * kPad);
-    row[0] = pack8(f);
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int k = 1; k < kPad / 8; ++k) row[k] = z;
+    *(u32x4*)(g + p * kFew) = pack8(f);
   }
   sh[threadIdx.x] = s;
   __syncthreads();
@@ -616,32 +672,48 @@ __global__ void scale_out_kernel(const float* __restrict__ y, const double* __re
 // optimiser and weight packing
 // ---------------------------------------------------------------------------
 
-__global__ void adam_kernel(float* __restrict__ prm, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, int64_t n, float lr, float c1, float c2) {
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    prm[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-  }
-}
+// where each layer's weights lie in the parameter vector and in the two
+// bfloat16 copies that the convolutions read
+struct PackArgs {
+  struct Item {
+    int64_t w_off;
+    int ci, co;
+    uint16_t* w_orig;  // [9][ci][co]
+    uint16_t* wt;      // [9][co][ci]
+  } l[kLayers];
+  int64_t n;           // parameters
+};
 
-// w [9][ci][co] float -> w_orig [9][ci][co] and wt [9][co][ci] bfloat16
-__global__ void pack_kernel(const float* __restrict__ w, int ci, int co, uint16_t* __restrict__ w_orig,
-                            uint16_t* __restrict__ wt) {
-  const int64_t n = (int64_t)9 * ci * co;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+// Adam on every parameter (or, step 0, none), and the bfloat16 copies of the
+// weights; one launch for all layers.
+__global__ void adam_pack_kernel(PackArgs a, int step, float* __restrict__ prm, const float* __restrict__ g,
+                                 float* __restrict__ m, float* __restrict__ v, float lr, float c1, float c2) {
+  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const int t = (int)(i / ((int64_t)ci * co));
-    const int rem = (int)(i - (int64_t)t * ci * co);
-    const int a = rem / co, b = rem - (rem / co) * co;
-    const uint16_t h = f2bf(w[i]);
-    w_orig[i] = h;
-    wt[((int64_t)t * co + b) * ci + a] = h;
+    float p = prm[i];
+    if (step) {
+      const float gi = g[i];
+      const float mi = b1 * m[i] + (1.f - b1) * gi;
+      const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+      m[i] = mi;
+      v[i] = vi;
+      p -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+      prm[i] = p;
+    }
+    int k = 0;
+#pragma unroll
+    for (int j = 1; j < kLayers; ++j) k = i >= a.l[j].w_off ? j : k;
+    const PackArgs::Item& ly = a.l[k];
+    const int64_t o = i - ly.w_off;
+    if (o < (int64_t)9 * ly.ci * ly.co) {  // a weight, not a bias
+      const int t = (int)(o / ((int64_t)ly.ci * ly.co));
+      const int rem = (int)(o - (int64_t)t * ly.ci * ly.co);
+      const int ci = rem / ly.co, co = rem - ci * ly.co;
+      const uint16_t h = f2bf(p);
+      ly.w_orig[o] = h;
+      ly.wt[((int64_t)t * ly.co + co) * ly.ci + ci] = h;
+    }
   }
 }
 
@@ -707,9 +779,9 @@ hipError_t conv_cin(const ConvArgs& a, int64_t P, hipStream_t st) {
 }
 
 hipError_t conv(const uint16_t* in, const uint16_t* wt, const float* bias, const ConvOut& o, int64_t P, int h,
-                int w, int cin, int cout, bool flip, bool up, hipStream_t st) {
-  const ConvArgs a{in, wt, bias, o.out, o.out2, o.skip, o.mask, o.f32, h, w, cout, up ? 1 : 0, flip ? 1 : 0,
-                   o.relu ? 1 : 0};
+                int w, int cin, int cout, bool flip, bool up, hipStream_t st, bool few = false) {
+  const ConvArgs a{in, wt, bias, o.out, o.out2, o.skip, o.mask, o.f32, h, w, cout, few ? kFew : cin,
+                   up ? 1 : 0, flip ? 1 : 0, o.relu ? 1 : 0};
   switch (cin) {
     case 32: return conv_cin<32>(a, P, st);
     case 64: return conv_cin<64>(a, P, st);
@@ -739,21 +811,27 @@ int wgrad_chunks(int64_t P, int cin, int cout) {
   return chunks(P, (int)std::min(want, cap));
 }
 
-hipError_t wgrad(const uint16_t* in, const uint16_t* g, float* part, float* dw, int64_t P, int h, int w,
-                 int cin, int cout, bool up, hipStream_t st) {
-  const int nch = wgrad_chunks(P, cin, cout);
-  WgradArgs a{in, g, part, h, w, cin, cout, up ? 1 : 0, P / nch};
-  hipLaunchKernelGGL(wgrad_kernel, dim3(nch, (cin / 32) * (cout / 32)), dim3(256), 0, st, a);
+// weight gradient, and with db the bias gradient
+hipError_t wgrad(const uint16_t* in, const uint16_t* g, float* part, float* dw, float* db, int64_t P, int h,
+                 int w, int cin, int cout, bool up, hipStream_t st, int cs = 0, int gcs = 0) {
+  const int nch = wgrad_chunks(P, cin, cout), tiles = (cin / 32) * (cout / 32);
+  const int nchb = db ? chunks(P, 256) : 0;
   const int64_t n = (int64_t)9 * cin * cout;
-  hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, part, nch, n, dw);
-  return hipGetLastError();
-}
-
-hipError_t bias_grad(const uint16_t* g, float* part, float* db, int64_t P, int cout, hipStream_t st) {
-  const int nch = chunks(P, 256);
-  hipLaunchKernelGGL(colsum_kernel, dim3(nch), dim3(256), 0, st, g, cout, P / nch, part);
-  hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)((cout + 31) / 32)), dim3(256), 0, st, part, nch,
-                     (int64_t)cout, db);
+  float* part_b = part + (int64_t)nch * n;
+  const WgradArgs a{in, g, part, part_b, h, w, cin, cout, cs ? cs : cin, gcs ? gcs : cout,
+                    up ? 1 : 0, nch, P / nch, db ? P / nchb : 0};
+  const dim3 grid(nch * tiles + nchb);
+  if (w >= 64)
+    hipLaunchKernelGGL(wgrad_kernel<64>, grid, dim3(256), 0, st, a);
+  else if (w == 32)
+    hipLaunchKernelGGL(wgrad_kernel<32>, grid, dim3(256), 0, st, a);
+  else if (w == 16)
+    hipLaunchKernelGGL(wgrad_kernel<16>, grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(wgrad_kernel<8>, grid, dim3(256), 0, st, a);
+  const int nb = (int)((n + 31) / 32), nbb = db ? (cout + 31) / 32 : 0;
+  hipLaunchKernelGGL(chunk_sum_kernel, dim3(nb + nbb), dim3(256), 0, st, SumArgs{part, dw, n, nch},
+                     SumArgs{part_b, db, cout, nchb}, nb);
   return hipGetLastError();
 }
 
@@ -810,7 +888,7 @@ struct Net {
   float* m = nullptr;
   float* v = nullptr;
   // activations per level (P_l = nmax * (h >> l) * (w >> l) pixels)
-  uint16_t* x = nullptr;                 // features [P_0][32]
+  uint16_t* x = nullptr;                 // features [P_0][8]
   uint16_t* ein[kLevels] = {};           // encoder input (l > 0: pooled)
   uint16_t* eh[kLevels] = {};
   uint16_t* ee[kLevels] = {};
@@ -820,7 +898,7 @@ struct Net {
   uint16_t* gen[kLevels] = {};           // gradient with respect to e_l
   uint16_t* g1[kLevels] = {};            // gradient scratch, 128 channels
   uint16_t* g2[kLevels] = {};
-  uint16_t* gy = nullptr;                // [P_0][32]
+  uint16_t* gy = nullptr;                // [P_0][8]
   float* yf = nullptr;                   // [P_0]
   float* tgt = nullptr;                  // [P_0]
   double* sig2 = nullptr;                // [nmax]
@@ -872,7 +950,7 @@ wf_status create_net(const wf_nn_shape* s, Net** out) {
     NA(ly.wt, (size_t)9 * ly.ci * ly.co * 2);
   }
   const int64_t P0 = (int64_t)n->nmax * n->h * n->w;
-  NA(n->x, P0 * kPad * 2);
+  NA(n->x, P0 * kFew * 2);
   for (int l = 0; l < kLevels; ++l) {
     const int64_t Pl = P0 >> (2 * l);
     const int c = kChan[l];
@@ -890,12 +968,12 @@ wf_status create_net(const wf_nn_shape* s, Net** out) {
     NA(n->g2[l], Pl * 128 * 2);
   }
   n->ein[0] = n->x;
-  NA(n->gy, P0 * kPad * 2);
+  NA(n->gy, P0 * kFew * 2);
   NA(n->yf, P0 * 4);
   NA(n->tgt, P0 * 4);
   NA(n->sig2, n->nmax * 8);
   NA(n->rowm, (size_t)n->nmax * n->h * 8);
-  NA(n->part, (size_t)kPartFloats * 4);
+  NA(n->part, (size_t)(kPartFloats + 256 * 128) * 4);  // and the bias sums' partials
   NA(n->lpart, 1024 * 8);
   NA(n->loss, 8);
 #undef NA
@@ -911,10 +989,19 @@ wf_status create_net(const wf_nn_shape* s, Net** out) {
   return WF_OK;
 }
 
-hipError_t pack_all(Net* n, hipStream_t st) {
-  for (auto& ly : n->L)
-    hipLaunchKernelGGL(pack_kernel, dim3(grid_for((int64_t)9 * ly.ci * ly.co)), dim3(256), 0, st,
-                       n->prm + ly.w_off, ly.ci, ly.co, ly.w_orig, ly.wt);
+// one Adam step with learning rate lr (or, lr = 0, none) and the weights' copies
+hipError_t adam_pack(Net* n, float lr, hipStream_t st) {
+  PackArgs a;
+  for (int k = 0; k < kLayers; ++k) a.l[k] = {n->L[k].w_off, n->L[k].ci, n->L[k].co, n->L[k].w_orig, n->L[k].wt};
+  a.n = n->nparam;
+  float c1 = 0.f, c2 = 0.f;
+  if (lr > 0.f) {
+    n->adam_t += 1;
+    c1 = (float)(1.0 / (1.0 - std::pow(0.9, n->adam_t)));
+    c2 = (float)(1.0 / (1.0 - std::pow(0.999, n->adam_t)));
+  }
+  hipLaunchKernelGGL(adam_pack_kernel, dim3(grid_for(n->nparam)), dim3(256), 0, st, a, lr > 0.f ? 1 : 0, n->prm,
+                     n->grad, n->m, n->v, lr, c1, c2);
   return hipGetLastError();
 }
 
@@ -936,7 +1023,8 @@ wf_status forward(Net* n, int nb, bool keep, hipStream_t st) {
     if (l > 0) NN_TRY(ew(EW_POOL, n->ee[l - 1], nullptr, n->ein[l], Pl, hl, wl, cin, st));
     const Layer& a = n->L[k];
     const Layer& b = n->L[k + 1];
-    NN_TRY(conv(n->ein[l], a.wt, n->prm + a.b_off, relu(n->eh[l]), Pl, hl, wl, a.ci, a.co, false, false, st));
+    NN_TRY(conv(n->ein[l], a.wt, n->prm + a.b_off, relu(n->eh[l]), Pl, hl, wl, a.ci, a.co, false, false, st,
+                l == 0));
     NN_TRY(conv(n->eh[l], b.wt, n->prm + b.b_off, relu(n->ee[l]), Pl, hl, wl, b.ci, b.co, false, false, st));
     k += 2;
   }
@@ -973,20 +1061,20 @@ wf_status backward(Net* n, int nb, hipStream_t st) {
   NN_TRY(hipGetLastError());
   // adjoint of layer ly in its input, masked where the activation is not positive
   auto adjoint = [&](const Layer& ly, const uint16_t* g, uint16_t* out, uint16_t* masked,
-                     const uint16_t* act, int64_t P, int h, int w) {
+                     const uint16_t* act, int64_t P, int h, int w, bool few = false) {
     ConvOut o;
     o.out = out ? out : masked;
     o.out2 = out ? masked : nullptr;
     o.mask = act;
-    return conv(g, ly.w_orig, nullptr, o, P, h, w, ly.co, ly.ci, true, false, st);
+    return conv(g, ly.w_orig, nullptr, o, P, h, w, ly.co, ly.ci, true, false, st, few);
   };
   int k = kLayers - 1;
   uint16_t* gu = n->g1[0];  // gradient of u_l's pre-activation
   {
     const Layer& o = n->L[k];
-    NN_TRY(wgrad(n->du[0], n->gy, n->part, n->grad + o.w_off, P0, n->h, n->w, o.ci, o.co, false, st));
-    NN_TRY(bias_grad(n->gy, n->part, n->grad + o.b_off, P0, o.co, st));
-    NN_TRY(adjoint(o, n->gy, nullptr, gu, n->du[0], P0, n->h, n->w));
+    NN_TRY(wgrad(n->du[0], n->gy, n->part, n->grad + o.w_off, n->grad + o.b_off, P0, n->h, n->w, o.ci, o.co, false,
+                 st, 0, kFew));
+    NN_TRY(adjoint(o, n->gy, nullptr, gu, n->du[0], P0, n->h, n->w, true));
   }
   k -= 1;
   for (int l = 0; l < kLevels - 1; ++l) {
@@ -994,14 +1082,12 @@ wf_status backward(Net* n, int nb, hipStream_t st) {
     const int hl = n->h >> l, wl = n->w >> l;
     const Layer& b = n->L[k];      // second convolution of decoder level l
     const Layer& a = n->L[k - 1];  // first one
-    NN_TRY(wgrad(n->dc[l], gu, n->part, n->grad + b.w_off, Pl, hl, wl, b.ci, b.co, false, st));
-    NN_TRY(bias_grad(gu, n->part, n->grad + b.b_off, Pl, b.co, st));
+    NN_TRY(wgrad(n->dc[l], gu, n->part, n->grad + b.w_off, n->grad + b.b_off, Pl, hl, wl, b.ci, b.co, false, st));
     // gradient with respect to c_l = b_l + e_l: to the skip, and to b_l
     uint16_t* gb = n->g2[l];
     NN_TRY(adjoint(b, gu, n->gen[l], gb, n->db[l], Pl, hl, wl));
-    NN_TRY(wgrad(l + 1 < kLevels - 1 ? n->du[l + 1] : n->ee[l + 1], gb, n->part, n->grad + a.w_off, Pl, hl, wl,
+    NN_TRY(wgrad(l + 1 < kLevels - 1 ? n->du[l + 1] : n->ee[l + 1], gb, n->part, n->grad + a.w_off, n->grad + a.b_off, Pl, hl, wl,
                  a.ci, a.co, true, st));
-    NN_TRY(bias_grad(gb, n->part, n->grad + a.b_off, Pl, a.co, st));
     uint16_t* ga = n->g1[l];
     NN_TRY(adjoint(a, gb, ga, nullptr, nullptr, Pl, hl, wl));
     // adjoint of the upsampling: gradient with respect to u_{l+1}
@@ -1016,11 +1102,10 @@ wf_status backward(Net* n, int nb, hipStream_t st) {
     const int hl = n->h >> l, wl = n->w >> l;
     const Layer& a = n->L[2 * l];
     const Layer& b = n->L[2 * l + 1];
-    NN_TRY(wgrad(n->eh[l], n->gen[l], n->part, n->grad + b.w_off, Pl, hl, wl, b.ci, b.co, false, st));
-    NN_TRY(bias_grad(n->gen[l], n->part, n->grad + b.b_off, Pl, b.co, st));
+    NN_TRY(wgrad(n->eh[l], n->gen[l], n->part, n->grad + b.w_off, n->grad + b.b_off, Pl, hl, wl, b.ci, b.co, false, st));
     NN_TRY(adjoint(b, n->gen[l], nullptr, n->g1[l], n->eh[l], Pl, hl, wl));
-    NN_TRY(wgrad(n->ein[l], n->g1[l], n->part, n->grad + a.w_off, Pl, hl, wl, a.ci, a.co, false, st));
-    NN_TRY(bias_grad(n->g1[l], n->part, n->grad + a.b_off, Pl, a.co, st));
+    NN_TRY(wgrad(n->ein[l], n->g1[l], n->part, n->grad + a.w_off, n->grad + a.b_off, Pl, hl, wl, a.ci, a.co, false, st,
+                 l == 0 ? kFew : 0));
     if (l > 0) {
       NN_TRY(adjoint(a, n->g1[l], n->g2[l], nullptr, nullptr, Pl, hl, wl));
       NN_TRY(ew(EW_ADD_POOL_ADJ, n->g2[l], n->ee[l - 1], n->gen[l - 1], Pl << 2, hl * 2, wl * 2, kChan[l - 1], st));
@@ -1033,7 +1118,7 @@ template <class T>
 wf_status prepare(Net* n, int nb, const void* d, const void* npix, const uint8_t* mask, const void* s,
                   hipStream_t st) {
   const int64_t hw = (int64_t)n->h * n->w, P0 = nb * hw;
-  constexpr int kSlices = 32;  // divides every supported map size
+  constexpr int kSlices = 128;  // divides every supported map size
   hipLaunchKernelGGL(sigma_kernel<T>, dim3(nb, kSlices), dim3(256), 0, st, (const T*)npix, mask, hw,
                      (double*)n->part);
   hipLaunchKernelGGL(sigma_final_kernel, dim3((nb + 63) / 64), dim3(64), 0, st, (const double*)n->part,
@@ -1042,17 +1127,6 @@ wf_status prepare(Net* n, int nb, const void* d, const void* npix, const uint8_t
   hipLaunchKernelGGL(features_kernel<T>, dim3(grid_for(P0)), dim3(256), 0, st, (const T*)d, (const T*)npix,
                      mask, (const T*)s, n->sig2, n->rowm, n->w, hw, P0, n->x, s ? n->tgt : nullptr);
   NN_TRY(hipGetLastError());
-  return WF_OK;
-}
-
-wf_status adam(Net* n, float lr, hipStream_t st) {
-  n->adam_t += 1;
-  const float c1 = (float)(1.0 / (1.0 - std::pow(0.9, n->adam_t)));
-  const float c2 = (float)(1.0 / (1.0 - std::pow(0.999, n->adam_t)));
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n->nparam)), dim3(256), 0, st, n->prm, n->grad, n->m, n->v,
-                     n->nparam, lr, c1, c2);
-  NN_TRY(hipGetLastError());
-  NN_TRY(pack_all(n, st));
   return WF_OK;
 }
 
@@ -1103,7 +1177,7 @@ wf_status wf_nn_set_params(void* net, const float* params, hipStream_t stream) {
   NN_TRY(hipMemsetAsync(n->m, 0, n->nparam * 4, stream));
   NN_TRY(hipMemsetAsync(n->v, 0, n->nparam * 4, stream));
   n->adam_t = 0;
-  NN_TRY(pack_all(n, stream));
+  NN_TRY(adam_pack(n, 0.f, stream));
   NN_TRY(hipStreamSynchronize(stream));
   return WF_OK;
 }
@@ -1147,7 +1221,7 @@ wf_status wf_nn_train_step(void* net, int32_t nb, const void* d, const void* n_p
   if (st != WF_OK) return st;
   if ((st = forward(n, nb, true, stream)) != WF_OK) return st;
   if ((st = backward(n, nb, stream)) != WF_OK) return st;
-  if ((st = adam(n, lr, stream)) != WF_OK) return st;
+  NN_TRY(adam_pack(n, lr, stream));
   return read_loss(n, loss, stream);
 }
 
@@ -1191,7 +1265,7 @@ wf_status wf_nn_conv3x3(int32_t mode, int32_t nb, int32_t h, int32_t w, int32_t 
     if (!g) return WF_EINVAL;
     float* part = nullptr;
     NN_TRY(hipMalloc((void**)&part, (size_t)wgrad_chunks(P, ci, co) * 9 * ci * co * 4));
-    hipError_t e = wgrad(in, g, part, (float*)out, P, h, w, ci, co, false, stream);
+    hipError_t e = wgrad(in, g, part, (float*)out, nullptr, P, h, w, ci, co, false, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     (void)hipFree(part);
     return from_hip(e);
