@@ -301,7 +301,7 @@ struct twp_offsets {
 
 // Natural-table index of entry e of the pass-major table of plan_for<N, E>.
 template <int N, int E>
-__device__ __forceinline__ int twp_source(int e) {
+__host__ __device__ __forceinline__ int twp_source(int e) {
   using PL = plan_for<N, E>;
   using O = twp_offsets<N, E>;
   if (e < O::o3) {

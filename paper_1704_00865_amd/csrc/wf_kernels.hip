@@ -395,20 +395,25 @@ __device__ __forceinline__ void copy16(WF_GLOBAL cx<T>* dst, const cx<T>* src) {
 // row kernel: inverse row FFT -> white-level update -> forward row FFT
 // ---------------------------------------------------------------------------
 // twiddle table staged in LDS, in the pass-major order of the kernel's radix
-// plan, when it is small (float32 up to 2048 points); larger tables are read
-// in natural order through the L1/L2 caches
+// plan, when it is small (float32, and float64 up to 1024 points; at 4096
+// float32 points 32 KB in LDS take the column kernel from 128 to 105 us per
+// launch at 4096^2).  Larger ones (float64, 2048 points, where the LDS would
+// hold one block per CU: 13.4 to 15.7 ms per 200 sweeps) are read through the
+// caches, in the same order, so that the lanes of a read fall on few lines
+// (13.4 to 11.6 ms): the context holds the sweep's and the monitor's tables behind the
+// natural one
 template <class T, int N>
 constexpr bool lds_twiddles() {
-  return N * 2 * (int)sizeof(T) <= 16384;
+  return N * 2 * (int)sizeof(T) <= (sizeof(T) == 4 ? 32768 : 16384);
 }
 
 // values per thread of the row kernel's transforms: 8 for the float32
-// lengths 1024 and 2048 (twice the threads of 16 values, so twice the waves
-// to hide the row kernel's memory latency; measured 6% faster at 2048), else
-// the default (at 4096, 8 values would make 1024-thread blocks that spill)
+// lengths from 1024 on (twice the threads of 16 values, so twice the waves
+// to hide the row kernel's memory latency; measured 6% faster at 2048; at 4096
+// with two rows per block, see tile_rows), else the default
 template <class T, int N>
 constexpr int row_elems() {
-  return (sizeof(T) == 4 && (N == 1024 || N == 2048)) ? 8 : elems<N>::value;
+  return (sizeof(T) == 4 && (N == 1024 || N == 2048 || N == 4096)) ? 8 : elems<N>::value;
 }
 
 // values per thread of the column kernel's transforms: 8 for the float32
@@ -575,7 +580,7 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
     }
     __syncthreads();
     if constexpr (LTW) fft<T, NX, true, E, true>(reg, lds + p * XS, t, (const cx<T>*)twl);
-    else fft<T, NX, true, E, false>(reg, lds + p * XS, t, twg);
+    else fft<T, NX, true, E, true>(reg, lds + p * XS, t, twg + NX);
     const T sc = (T)a.scale;
     if constexpr (MODE == ROW_C2R) {
 #pragma unroll
@@ -615,7 +620,7 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
     if constexpr (LTW) __syncthreads();
   }
   if constexpr (LTW) fft<T, NX, false, E, true>(reg, lds + p * XS, t, (const cx<T>*)twl);
-  else fft<T, NX, false, E, false>(reg, lds + p * XS, t, twg);
+  else fft<T, NX, false, E, true>(reg, lds + p * XS, t, twg + NX);
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[p * XS + LM::at_tq(t, q)] = reg[q];
   __syncthreads();
@@ -898,7 +903,7 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
     for (int q = 0; q < E; ++q) reg[q] = lds[c * YS + LM::at_tq(t, q)];
     __syncthreads();
     if constexpr (LTW) fft<T, NY, false, E, true>(reg, lds + c * YS, t, (const cx<T>*)twl);
-    else fft<T, NY, false, E, false>(reg, lds + c * YS, t, twg);
+    else fft<T, NY, false, E, true>(reg, lds + c * YS, t, twg + NY);
   }
 
   // packed column (block 0, column 0): split Z = C0 + i CN into the k_x = 0
@@ -1076,7 +1081,7 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
       gmem(a.jpart)[a.jrow + g] = sum_partials(jsh, blockDim.x) * a.scale;
   }
   if constexpr (LTW) fft<T, NY, true, E, true>(reg, lds + c * YS, t, (const cx<T>*)twl);
-  else fft<T, NY, true, E, false>(reg, lds + c * YS, t, twg);
+  else fft<T, NY, true, E, true>(reg, lds + c * YS, t, twg + NY);
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg[q];
   __syncthreads();
@@ -1133,7 +1138,7 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
         cx<T>* reg2 = field == 0 ? rx : ry;
         WF_GLOBAL cx<T>* dst = gmem((cx<T>*)(field == 0 ? a.Mx : a.My));
         if constexpr (LTW) fft<T, NY, true, E, true>(reg2, lds + c * YS, t, (const cx<T>*)twl);
-        else fft<T, NY, true, E, false>(reg2, lds + c * YS, t, twg);
+        else fft<T, NY, true, E, true>(reg2, lds + c * YS, t, twg + NY);
 #pragma unroll
         for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg2[q];
         __syncthreads();
@@ -1240,7 +1245,7 @@ __global__ __launch_bounds__(kTCM * (NY / mon_elems<NY>())) void mon_col_kernel(
     cx<T>* reg = field == 0 ? rx : ry;
     WF_GLOBAL cx<T>* dst = gmem((cx<T>*)(field == 0 ? m.Mx : m.My));
     if constexpr (LTW) fft<T, NY, true, E, true>(reg, lds + c * YS, t, (const cx<T>*)twl);
-    else fft<T, NY, true, E, false>(reg, lds + c * YS, t, twg);
+    else fft<T, NY, true, E, true>(reg, lds + c * YS, t, twg + 2 * NY);
 #pragma unroll
     for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg[q];
     __syncthreads();
@@ -1367,7 +1372,7 @@ __global__ __launch_bounds__(kRWM * (NX / mon_elems<NX>())) void mon_row_kernel(
   }
   __syncthreads();
   if constexpr (LTW) fft<T, NX, true, E, true>(reg, lds + r * XS, t, (const cx<T>*)twl);
-  else fft<T, NX, true, E, false>(reg, lds + r * XS, t, twg);
+  else fft<T, NX, true, E, true>(reg, lds + r * XS, t, twg + 2 * NX);
   double a_dd = 0.0, a_mx = 0.0;
 #pragma unroll
   for (int q = 0; q < E; ++q) {

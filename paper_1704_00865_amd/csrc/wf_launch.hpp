@@ -14,6 +14,21 @@ struct TileCfg {
 constexpr int kNumTiles = 7;
 constexpr int kTileDefault = 1;
 extern const TileCfg kTiles[kNumTiles];
+// Rows per row block.  Two where four rows' bands fill the LDS of a CU, so that
+// several blocks share it and one's transforms run beside the others' loads: at
+// 4096 float32 points (65 KB with the twiddle table; four rows take 98 KB, one
+// block per CU: 79 us per launch at 4096^2, two rows 67) and at 2048 float64
+// points (33 KB instead of 66: 200 sweeps at 2048^2 11.6 to 11.4 ms).
+inline int tile_rows(int tile, int nx, int esz) {
+  return (tile == kTileDefault && nx * esz >= 16384) ? 2 : kTiles[tile].RW;
+}
+
+// Tables of n twiddles each that a context holds for a length: the natural one,
+// and, where the kernels do not stage it in LDS (see lds_twiddles), the
+// pass-major ones of the sweep and of the monitor.  order: natural-table index
+// of each of their entries (0 past their end).
+int twiddle_tables(int n, int esz);
+void twiddle_order(int n, int esz, int* sweep, int* monitor);
 
 // Every launch covers nmaps maps of one shape and chain kind: argv is a
 // DEVICE array of nmaps argument blocks (blockIdx.y selects one); a / m is a

@@ -116,8 +116,8 @@ void for_each_buffer(Ctx* c, F take) {
   take((void**)&c->sy, modes * esz);
   take((void**)&c->sig, modes * esz);
   take((void**)&c->nbar2, ny * nx * esz);
-  take((void**)&c->twx, nx * 2 * esz);
-  take((void**)&c->twy, ny * 2 * esz);
+  take((void**)&c->twx, twiddle_tables(c->nx, (int)esz) * nx * 2 * esz);
+  take((void**)&c->twy, twiddle_tables(c->ny, (int)esz) * ny * 2 * esz);
   take((void**)&c->Mx, ny * c->kpm * 2 * esz);
   take((void**)&c->My, ny * c->kpm * 2 * esz);
   take((void**)&c->part, std::max<size_t>(2 * ny / kRWM, 16 * kStatBlocks) * sizeof(double));
@@ -160,14 +160,26 @@ int supported(int ny, int nx, int prec) {
   return length_ok(ny, prec) && length_ok(nx, prec);
 }
 
+// Twiddle tables of one length into out: w_n^j in natural order, computed in
+// double and rounded once, then the pass-major ones that the length has.
+// Returns their size in complex values.
 template <class T>
-void make_table(std::vector<T>& out, int n) {
-  out.resize(2 * (size_t)n);
+size_t make_table(T* out, int n) {
   for (int j = 0; j < n; ++j) {
     const double ang = 2.0 * M_PI * (double)j / (double)n;
     out[2 * j] = (T)std::cos(ang);
     out[2 * j + 1] = (T)(-std::sin(ang));
   }
+  const size_t size = (size_t)twiddle_tables(n, sizeof(T)) * n;
+  if (size > (size_t)n) {
+    std::vector<int> order(size - n);
+    twiddle_order(n, sizeof(T), order.data(), order.data() + n);
+    for (size_t e = 0; e < order.size(); ++e) {
+      out[2 * (n + e)] = out[2 * order[e]];
+      out[2 * (n + e) + 1] = out[2 * order[e] + 1];
+    }
+  }
+  return size;
 }
 
 void free_ctx(Ctx* c) {
@@ -232,20 +244,17 @@ wf_status create(const wf_shape* sh, Ctx** out) {
     free_ctx(c);
     return from_hip(e);
   }
-  // twiddle tables, computed in double and rounded once
-  if (c->prec == WF_F64) {
-    std::vector<double> tdx, tdy;
-    make_table(tdx, c->nx);
-    make_table(tdy, c->ny);
-    e = hipMemcpy(c->twx, tdx.data(), tdx.size() * 8, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->twy, tdy.data(), tdy.size() * 8, hipMemcpyHostToDevice);
-  } else {
-    std::vector<float> fx, fy;
-    make_table(fx, c->nx);
-    make_table(fy, c->ny);
-    e = hipMemcpy(c->twx, fx.data(), fx.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->twy, fy.data(), fy.size() * 4, hipMemcpyHostToDevice);
-  }
+  auto tables = [&](auto zero) {
+    using T = decltype(zero);
+    std::vector<T> t(6 * (size_t)std::max(c->nx, c->ny));
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+      const int n = i == 0 ? c->nx : c->ny;
+      const size_t size = make_table(t.data(), n);
+      e = hipMemcpy(i == 0 ? c->twx : c->twy, t.data(), size * 2 * sizeof(T), hipMemcpyHostToDevice);
+    }
+  };
+  if (c->prec == WF_F64) tables(0.0);
+  else tables(0.0f);
   if (e != hipSuccess) {
     free_ctx(c);
     return from_hip(e);
@@ -353,7 +362,7 @@ SweepArgs<T> sweep_args(Ctx* c, const wf_inputs* in, const Chain& ch) {
   a.tauW = ch.tauW;
   a.cB = ch.cB;
   a.scale = 1.0 / ((double)c->nx * (double)c->ny);
-  a.jrow = c->ny / kTiles[c->tile].RW;
+  a.jrow = c->ny / tile_rows(c->tile, c->nx, (int)c->esz);
   a.jpart = c->jpart;
   a.sy = (const T*)c->sy;
   a.Mx = c->Mx;
@@ -365,7 +374,7 @@ SweepArgs<T> sweep_args(Ctx* c, const wf_inputs* in, const Chain& ch) {
 // joint-objective partials of one sweep: row blocks, then column blocks
 int j_blocks(const Ctx* c) {
   const TileCfg& t = kTiles[c->tile];
-  return c->ny / t.RW + (c->nx / 2) / t.TC;
+  return c->ny / tile_rows(c->tile, c->nx, (int)c->esz) + (c->nx / 2) / t.TC;
 }
 
 // Sweeps launched with the joint-objective variants: those that can close a
@@ -1159,19 +1168,11 @@ wf_status solve_noalloc_t(const wf_shape* sh, const wf_inputs* in, const wf_sche
   c.h_args = h_args;
   c.h_margs = h_margs;
   c.h_ctrl = h_ctrl;
-  // twiddle tables (the largest supported length is 4096), computed in
-  // double and rounded once, as for a context
-  static thread_local T tw[2][2 * 4096];
-  for (int a = 0; a < 2; ++a) {
-    const int n = a == 0 ? c.nx : c.ny;
-    for (int j = 0; j < n; ++j) {
-      const double ang = 2.0 * M_PI * (double)j / (double)n;
-      tw[a][2 * j] = (T)std::cos(ang);
-      tw[a][2 * j + 1] = (T)(-std::sin(ang));
-    }
-  }
-  WF_TRY(hipMemcpyAsync(c.twx, tw[0], (size_t)c.nx * 2 * sizeof(T), hipMemcpyHostToDevice, st));
-  WF_TRY(hipMemcpyAsync(c.twy, tw[1], (size_t)c.ny * 2 * sizeof(T), hipMemcpyHostToDevice, st));
+  // twiddle tables (the largest supported length is 4096), as for a context
+  static thread_local T tw[2][6 * 4096];
+  const size_t sx = make_table(tw[0], c.nx), sy = make_table(tw[1], c.ny);
+  WF_TRY(hipMemcpyAsync(c.twx, tw[0], sx * 2 * sizeof(T), hipMemcpyHostToDevice, st));
+  WF_TRY(hipMemcpyAsync(c.twy, tw[1], sy * 2 * sizeof(T), hipMemcpyHostToDevice, st));
   const wf_status r = solve_t<T>(&c, in, sch, s_init, s_out, rep, trace, st);
   (void)hipStreamSynchronize(st);  // the staging above is this call's memory
   return r;
