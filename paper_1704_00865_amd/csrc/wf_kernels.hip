@@ -244,16 +244,18 @@ __global__ __launch_bounds__(256) void stats_spectra_kernel(const T* __restrict_
   }
 }
 
-// reduce per-block statistics in a fixed order; ops[j] says how column j
-// combines (sum / min / max).  Wave j reduces column j: lane l takes blocks
-// l, l + 64, ..., then the lanes combine in a fixed butterfly.
-#if WF_PART & 1
+// reduce per-block statistics in a fixed order: block 0 the pixels' (partials
+// part, result out[0..7]), block 1 the spectra's (behind them); bit 2j of
+// its code says how column j combines (0 sum, 1 min, 2 max).  Wave j reduces
+// column j: lane l takes blocks l, l + 64, ..., then the lanes combine in a
+// fixed butterfly.
 __global__ __launch_bounds__(512) void stats_finalize_kernel(const double* __restrict__ part, int nblk,
-                                                             int4 ops_lo, int4 ops_hi,
-                                                             double* __restrict__ out) {
+                                                             int2 codes, double* __restrict__ out)
+#if WF_PART & 1
+{
   const int j = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ops[8] = {ops_lo.x, ops_lo.y, ops_lo.z, ops_lo.w, ops_hi.x, ops_hi.y, ops_hi.z, ops_hi.w};
-  const int op = ops[j];
+  const int op = ((blockIdx.x == 0 ? codes.x : codes.y) >> (2 * j)) & 3;
+  part += (size_t)8 * nblk * blockIdx.x;
   auto comb = [op](double a, double b) {
     return op == RED_SUM ? a + b : (op == RED_MIN ? fmin(a, b) : fmax(a, b));
   };
@@ -261,12 +263,10 @@ __global__ __launch_bounds__(512) void stats_finalize_kernel(const double* __res
   for (int b = lane; b < nblk; b += 64) r = comb(r, part[8 * b + j]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) r = comb(r, __shfl_xor(r, off, 64));
-  if (lane == 0) out[j] = r;
+  if (lane == 0) out[8 * blockIdx.x + j] = r;
 }
 #else
-__global__ __launch_bounds__(512) void stats_finalize_kernel(const double* __restrict__ part, int nblk,
-                                                             int4 ops_lo, int4 ops_hi,
-                                                             double* __restrict__ out);
+;
 #endif
 
 // ---------------------------------------------------------------------------
@@ -1559,6 +1559,13 @@ __global__ __launch_bounds__(256) void controller_kernel(const CtrlArgs* __restr
     s->have_prev = 1;
   }
   s->base = klast + 1;
+  if (HostView* v = ca.view) {
+    // (the host reads fin after it has waited for the stream: no fence, which
+    // would write back an L2)
+    if (s->done) v->fin = *s;
+    __hip_atomic_store(&v->progress, s->done ? -1 : klast + 1, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 #endif
 

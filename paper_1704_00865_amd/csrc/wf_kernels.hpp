@@ -131,6 +131,13 @@ struct MonArgs {
   float* rout;          // MON_REFINE: [ny][nx] right-hand side of the next solve
 };
 
+// What the host follows a single map's solve by: pinned host memory that the
+// controller writes (a copy and an event per chunk cost 20 us of idle GPU)
+struct HostView {
+  int32_t progress;    // sweeps checked so far, -1 once done
+  DevSched fin;        // the schedule's final state (valid once done)
+};
+
 // per-map arguments of the controller (one block per map)
 struct CtrlArgs {
   DevSched* sch;
@@ -140,6 +147,7 @@ struct CtrlArgs {
   double* trace;       // kTraceCols values per monitor record
   const double* jpart; // joint-objective partials of the chunk's last sweep
   int njblk;
+  HostView* view;      // or null
 };
 
 // columns of a trace record: sweep, lambda, rho, dd2, rho_mask, J

@@ -58,8 +58,8 @@ hipError_t launch_to_float(const double* src, int64_t n, float* dst, hipStream_t
 hipError_t launch_pair_sum(const double* part, int nblk, double* out, hipStream_t st);
 template <class T>
 hipError_t launch_stats(const T* d, const T* npix, const uint8_t* mask, const T* sk, const T* poof,
-                        const T* pst, int ny, int nx, double* part, int nblk, double* out_pix,
-                        double* out_spec, hipStream_t st);
+                        const T* pst, int ny, int nx, double* part, int nblk, double* out,
+                        hipStream_t st);
 template <class T>
 // per-pixel and per-mode coefficients; also zeroes the transit buffer zB and
 // the two per-mode state arrays zA, zT (the zero start)

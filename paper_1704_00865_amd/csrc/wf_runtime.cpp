@@ -3,10 +3,10 @@
 // C ABI declared in include/wf.h.
 //
 // The loop enqueues chunks of K sweeps (2 launches each), then the float64
-// monitor (2 launches) and the one-block controller that evaluates the
-// schedule on the device.  The host never waits inside a chunk: it copies the
-// controller's state to pinned memory after each chunk and checks it two
-// chunks later, so the GPU keeps a queue of work; sweeps enqueued after
+// monitor and the one-block controller that evaluates the schedule on the
+// device.  The host never waits inside a chunk: the controller writes its
+// progress to pinned memory and the host stays two chunks ahead of it, so the
+// GPU keeps a queue of work; sweeps enqueued after
 // convergence see the device's done flag and return at once, which keeps the
 // result identical whatever the run-ahead.
 #include <hip/hip_runtime.h>
@@ -17,6 +17,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "wf.h"
@@ -31,6 +32,15 @@ constexpr int kRing = 4;   // pinned readback slots
 constexpr int kLag = 2;    // chunks between enqueue and the host's check
 constexpr int kProfSlots = 512;
 constexpr int kStaticCheck = 4;  // chunks between host checks without events
+
+constexpr int kViewRecords = 4096;   // monitor records kept in pinned memory
+
+struct ArgBlock {
+  alignas(16) unsigned char args[sizeof(SweepArgs<double>)];
+  alignas(16) unsigned char margs[sizeof(MonArgs<double>)];
+  alignas(16) CtrlArgs ctrl;
+  alignas(16) DevSched sch;
+};
 
 struct Ctx {
   int ny = 0, nx = 0, prec = 0;
@@ -59,15 +69,17 @@ struct Ctx {
   double* trace = nullptr;
   int trace_cap = 0;
   void* alpha_sk = nullptr;  // flat signal spectrum for the inverse-noise weighting
-  void* d_args = nullptr;    // device argument blocks of the single-map launches
+  // the single-map launches' argument blocks and schedule: one device block
+  // (ArgBlock), its staging (pinned, or the call's own memory), and where in
+  // the device block each lies
+  void* d_blk = nullptr;
+  ArgBlock* h_blk = nullptr;
+  void* d_args = nullptr;
   void* d_margs = nullptr;
   void* d_ctrl = nullptr;
-  void* h_args = nullptr;    // pinned staging of the same
-  void* h_margs = nullptr;
-  void* h_ctrl = nullptr;
-  DevSched* h_ring = nullptr;  // pinned
+  HostView* view = nullptr;    // pinned; null without allocations
+  double* h_trace = nullptr;   // pinned, kViewRecords records; written by the controller
   double* h_stats = nullptr;   // pinned
-  hipEvent_t ev_ring[kRing] = {};
   int profiling = 0;
   std::vector<hipEvent_t> prof_ev;
   // workspace carved from the library's static scratch (wf_solve_noalloc):
@@ -125,10 +137,13 @@ void for_each_buffer(Ctx* c, F take) {
   // least 2 rows per row block and 2 columns per tile)
   take((void**)&c->jpart, (ny / 2 + nx / 4) * sizeof(double));
   take((void**)&c->stats, 16 * sizeof(double));
-  take((void**)&c->sch, sizeof(DevSched));
-  take((void**)&c->d_args, sizeof(SweepArgs<double>));
-  take((void**)&c->d_margs, sizeof(MonArgs<double>));
-  take((void**)&c->d_ctrl, sizeof(CtrlArgs));
+  take((void**)&c->d_blk, sizeof(ArgBlock));
+  if (ArgBlock* b = (ArgBlock*)c->d_blk) {
+    c->d_args = b->args;
+    c->d_margs = b->margs;
+    c->d_ctrl = &b->ctrl;
+    c->sch = &b->sch;
+  }
 }
 
 wf_status from_hip(hipError_t e) {
@@ -184,20 +199,17 @@ size_t make_table(T* out, int n) {
 
 void free_ctx(Ctx* c) {
   void* bufs[] = {c->B, c->tA, c->tB, c->sc, c->nbA, c->sy, c->sig, c->nbar2, c->twx, c->twy,
-                  c->Mx, c->My, c->part, c->jpart, c->stats, c->sch, c->lam, c->trace,
-                  c->alpha_sk, c->d_args, c->d_margs, c->d_ctrl, c->ref_d, c->ref_npix,
+                  c->Mx, c->My, c->part, c->jpart, c->stats, c->lam, c->trace,
+                  c->alpha_sk, c->d_blk, c->ref_d, c->ref_npix,
                   c->ref_sk, c->ref_poof, c->ref_pst, c->ref_out, c->ref_init, c->ref_margs};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
   if (c->batch_dev) (void)hipFree(c->batch_dev);
   if (c->batch_host) (void)hipHostFree(c->batch_host);
-  if (c->h_ring) (void)hipHostFree(c->h_ring);
+  if (c->view) (void)hipHostFree(c->view);
+  if (c->h_trace) (void)hipHostFree(c->h_trace);
   if (c->h_stats) (void)hipHostFree(c->h_stats);
-  if (c->h_args) (void)hipHostFree(c->h_args);
-  if (c->h_margs) (void)hipHostFree(c->h_margs);
-  if (c->h_ctrl) (void)hipHostFree(c->h_ctrl);
-  for (auto& e : c->ev_ring)
-    if (e) (void)hipEventDestroy(e);
+  if (c->h_blk) (void)hipHostFree(c->h_blk);
   for (auto& e : c->prof_ev)
     if (e) (void)hipEventDestroy(e);
   if (c->chunk_exec) (void)hipGraphExecDestroy(c->chunk_exec);
@@ -233,13 +245,11 @@ wf_status create(const wf_shape* sh, Ctx** out) {
     free_ctx(c);
     return st;
   }
-  hipError_t e = hipHostMalloc((void**)&c->h_ring, kRing * sizeof(DevSched), hipHostMallocDefault);
+  hipError_t e = hipHostMalloc((void**)&c->view, sizeof(HostView), hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->h_stats, 16 * sizeof(double), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc(&c->h_args, sizeof(SweepArgs<double>), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc(&c->h_margs, sizeof(MonArgs<double>), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipHostMalloc(&c->h_ctrl, sizeof(CtrlArgs), hipHostMallocDefault);
-  for (int i = 0; i < kRing && e == hipSuccess; ++i)
-    e = hipEventCreateWithFlags(&c->ev_ring[i], hipEventDisableTiming);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&c->h_blk, sizeof(ArgBlock), hipHostMallocDefault);
+  if (e == hipSuccess)
+    e = hipHostMalloc((void**)&c->h_trace, kViewRecords * kTraceCols * sizeof(double), hipHostMallocDefault);
   if (e != hipSuccess) {
     free_ctx(c);
     return from_hip(e);
@@ -462,7 +472,7 @@ template <class T>
 hipError_t enqueue_stats(Ctx* c, const wf_inputs* in, hipStream_t st) {
   hipError_t e = launch_stats<T>((const T*)in->d, (const T*)in->n_pix, in->mask, (const T*)in->s_k,
                                  (const T*)in->p_oof, (const T*)in->p_stripe, c->ny, c->nx,
-                                 c->part, kStatBlocks, c->stats, c->stats + 8, st);
+                                 c->part, kStatBlocks, c->stats, st);
   if (e != hipSuccess) return e;
   return hipMemcpyAsync(c->h_stats, c->stats, 16 * sizeof(double), hipMemcpyDeviceToHost, st);
 }
@@ -515,8 +525,10 @@ wf_status map_setup(Ctx* c, const wf_inputs* in, const wf_schedule* s, const voi
     if (as != WF_OK) return as;
     c->trace_cap = r.n_chunks;
   }
-  r.lam.assign(maxs + 1, 0.0);
-  for (int k = 0; k <= maxs; ++k)
+  // (adaptive: the controller fills each further chunk)
+  const int n_lam = s->kind == WF_SCHED_FIXED ? maxs : std::min(K, maxs);
+  r.lam.assign(n_lam + 1, 0.0);
+  for (int k = 0; k <= n_lam; ++k)
     r.lam[k] = s->kind == WF_SCHED_FIXED ? s->lambda[std::min(k, s->n_lambda - 1)] : s->lambda0;
   DevSched& h = r.h;
   h = DevSched{};
@@ -535,7 +547,8 @@ wf_status map_setup(Ctx* c, const wf_inputs* in, const wf_schedule* s, const voi
   h.lam_last = r.lam[0];
   WF_TRY(hipMemcpyAsync(c->lam, r.lam.data(), r.lam.size() * sizeof(double),
                         hipMemcpyHostToDevice, st));
-  WF_TRY(hipMemcpyAsync(dsched, &h, sizeof(h), hipMemcpyHostToDevice, st));
+  // (a context's own schedule goes with its argument block)
+  if (dsched != c->sch) WF_TRY(hipMemcpyAsync(dsched, &h, sizeof(h), hipMemcpyHostToDevice, st));
   r.a = sweep_args<T>(c, in, r.ch);
   r.a.sch = dsched;
   r.a.warm_chain = s->field_mode;
@@ -543,11 +556,11 @@ wf_status map_setup(Ctx* c, const wf_inputs* in, const wf_schedule* s, const voi
   r.m.sch = dsched;
   r.m.s_out = s_out;
   r.m.out_chain = s->field_mode;
-  r.ctrl = CtrlArgs{dsched, c->lam, c->part, c->ny / kRWM, c->trace, c->jpart, j_blocks(c)};
+  r.ctrl = CtrlArgs{dsched, c->lam, c->part, c->ny / kRWM, c->trace, c->jpart, j_blocks(c), nullptr};
   // initial state (the single-map argument block is used for the warm start)
   if (s_init) {
-    std::memcpy(c->h_args, &r.a, sizeof(r.a));
-    WF_TRY(hipMemcpyAsync(c->d_args, c->h_args, sizeof(r.a), hipMemcpyHostToDevice, st));
+    std::memcpy(c->h_blk->args, &r.a, sizeof(r.a));
+    WF_TRY(hipMemcpyAsync(c->d_args, c->h_blk->args, sizeof(r.a), hipMemcpyHostToDevice, st));
     WF_TRY(launch_row<T>(c->tile, ROW_R2C, r.a, (const SweepArgs<T>*)c->d_args, 1, 0,
                          (const T*)s_init, nullptr, st));
     WF_TRY(launch_col<T>(c->tile, COL_INIT, r.a, (const SweepArgs<T>*)c->d_args, 1, 0, nullptr,
@@ -661,6 +674,24 @@ wf_status chunk_graph(Ctx* c, std::vector<ShapeClass<T>>& cls, const std::vector
   return WF_OK;
 }
 
+// Waits until the controller has checked `sweeps` sweeps or is done.  Looks at
+// the stream now and then, so that a device error ends the wait.
+hipError_t wait_progress(HostView* v, int64_t sweeps, hipStream_t st, bool* done) {
+  for (unsigned n = 1;; ++n) {
+    const int p = __atomic_load_n(&v->progress, __ATOMIC_RELAXED);
+    if (p < 0) *done = true;
+    if (p < 0 || p >= sweeps) return hipSuccess;
+    if (n % (1u << 16) == 0) {
+      const hipError_t q = hipStreamQuery(st);
+      if (q != hipErrorNotReady) {  // idle: everything enqueued has run
+        *done = __atomic_load_n(&v->progress, __ATOMIC_RELAXED) < 0;
+        return q;
+      }
+      std::this_thread::yield();
+    }
+  }
+}
+
 template <class T>
 wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void* s_init,
                   void* s_out, wf_report* rep, double* trace, hipStream_t st,
@@ -670,13 +701,20 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
   wf_status ss = map_setup<T>(c, in, s, s_init, s_out, c->sch, r, st);
   if (ss != WF_OK) return ss;
   if (chain_out) *chain_out = r.ch;
-  // argument blocks for the single-map launches
-  std::memcpy(c->h_args, &r.a, sizeof(r.a));
-  std::memcpy(c->h_margs, &r.m, sizeof(r.m));
-  std::memcpy(c->h_ctrl, &r.ctrl, sizeof(r.ctrl));
-  WF_TRY(hipMemcpyAsync(c->d_args, c->h_args, sizeof(r.a), hipMemcpyHostToDevice, st));
-  WF_TRY(hipMemcpyAsync(c->d_margs, c->h_margs, sizeof(r.m), hipMemcpyHostToDevice, st));
-  WF_TRY(hipMemcpyAsync(c->d_ctrl, c->h_ctrl, sizeof(r.ctrl), hipMemcpyHostToDevice, st));
+  // argument blocks for the single-map launches; the records go to pinned
+  // memory where it holds them all
+  const bool viewed = c->view != nullptr;
+  const bool view_trace = viewed && r.n_chunks <= kViewRecords;
+  if (viewed) {
+    c->view->progress = 0;
+    r.ctrl.view = c->view;
+    if (view_trace) r.ctrl.trace = c->h_trace;
+  }
+  std::memcpy(c->h_blk->args, &r.a, sizeof(r.a));
+  std::memcpy(c->h_blk->margs, &r.m, sizeof(r.m));
+  c->h_blk->ctrl = r.ctrl;
+  c->h_blk->sch = r.h;
+  WF_TRY(hipMemcpyAsync(c->d_blk, c->h_blk, sizeof(ArgBlock), hipMemcpyHostToDevice, st));
   std::vector<ShapeClass<T>> cls(1);
   cls[0].maps = {0};
   cls[0].argv = (SweepArgs<T>*)c->d_args;
@@ -696,6 +734,7 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
   }
   const int prof_chunks = kProfSlots / 6;
   int launched = 0;
+  DevSched fin{};
   // without profiling (whose events are recorded by the dispatches of the
   // first sweeps) every chunk is the replayed graph
   hipGraphExec_t exec = nullptr;
@@ -712,36 +751,32 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
       if (es != WF_OK) return es;
     }
     launched = ci + 1;
-    if (c->no_alloc) {
-      // no events: every kStaticCheck chunks the host waits for the stream
-      // and reads the device schedule (plain host memory)
+    if (!viewed) {
+      // no pinned memory: every kStaticCheck chunks the host waits for the
+      // stream and reads the device schedule
       if ((ci + 1) % kStaticCheck == 0 && ci + 1 < r.n_chunks) {
-        WF_TRY(hipMemcpyAsync(c->h_ring, c->sch, sizeof(DevSched), hipMemcpyDeviceToHost, st));
+        WF_TRY(hipMemcpyAsync(&fin, c->sch, sizeof(fin), hipMemcpyDeviceToHost, st));
         WF_TRY(hipStreamSynchronize(st));
-        if (c->h_ring[0].done) break;
+        if (fin.done) break;
       }
-      continue;
-    }
-    const int slot = ci % kRing;
-    WF_TRY(hipMemcpyAsync(&c->h_ring[slot], c->sch, sizeof(DevSched), hipMemcpyDeviceToHost, st));
-    WF_TRY(hipEventRecord(c->ev_ring[slot], st));
-    if (ci >= kLag) {
-      const int chk = (ci - kLag) % kRing;
-      WF_TRY(hipEventSynchronize(c->ev_ring[chk]));
-      if (c->h_ring[chk].done) break;
+    } else if (ci >= kLag) {
+      bool done = false;
+      WF_TRY(wait_progress(c->view, std::min((ci - kLag + 1) * (int64_t)K, (int64_t)s->max_sweeps), st,
+                           &done));
+      if (done) break;
     }
   }
-  WF_TRY(hipStreamSynchronize(st));
-  DevSched fin;
-  WF_TRY(hipMemcpy(&fin, c->sch, sizeof(fin), hipMemcpyDeviceToHost));
-
   // output s = S x, x = t_A / (S_chain + T_A) at the last lambda
   WF_TRY(launch_mon_col<T>(r.m, cls[0].margv, 1, MON_OUTPUT, st));
   WF_TRY(launch_mon_row<T>(r.m, cls[0].margv, 1, MON_OUTPUT, st));
-  if (trace && fin.n_rec > 0)
-    WF_TRY(hipMemcpyAsync(trace, c->trace, (size_t)fin.n_rec * kTraceCols * sizeof(double),
-                          hipMemcpyDeviceToHost, st));
+  if (!viewed) WF_TRY(hipMemcpyAsync(&fin, c->sch, sizeof(fin), hipMemcpyDeviceToHost, st));
   WF_TRY(hipStreamSynchronize(st));
+  if (viewed) fin = c->view->fin;
+  if (trace && fin.n_rec > 0) {
+    const size_t bytes = (size_t)fin.n_rec * kTraceCols * sizeof(double);
+    if (view_trace) std::memcpy(trace, c->h_trace, bytes);
+    else WF_TRY(hipMemcpy(trace, c->trace, bytes, hipMemcpyDeviceToHost));
+  }
 
   if (rep) {
     fill_report(rep, fin, r.ch, r.pix);
@@ -990,6 +1025,7 @@ wf_status solve_refined(Ctx* c32, Ctx* c64, const wf_inputs* in, const wf_schedu
   MapRun<double>& r64 = runs[0];
   wf_status ss = map_setup<double>(c64, in, first, nullptr, s_out, c64->sch, r64, st);
   if (ss != WF_OK) return ss;
+  WF_TRY(hipMemcpyAsync(c64->sch, &r64.h, sizeof(r64.h), hipMemcpyHostToDevice, st));
   // float32 copies of the inputs
   WF_TRY(launch_to_float((const double*)in->d, (int64_t)npix, (float*)c32->ref_d, st));
   WF_TRY(launch_to_float((const double*)in->n_pix, (int64_t)npix, (float*)c32->ref_npix, st));
@@ -1158,16 +1194,10 @@ wf_status solve_noalloc_t(const wf_shape* sh, const wf_inputs* in, const wf_sche
   if (ss != WF_OK) return ss;
   carve_static(&c, base, lam_cap, trace_cap);
   // host staging in plain memory of this call
-  DevSched h_ring[kRing];
   double h_stats[16];
-  alignas(16) unsigned char h_args[sizeof(SweepArgs<double>)];
-  alignas(16) unsigned char h_margs[sizeof(MonArgs<double>)];
-  alignas(16) unsigned char h_ctrl[sizeof(CtrlArgs)];
-  c.h_ring = h_ring;
+  ArgBlock h_blk;
   c.h_stats = h_stats;
-  c.h_args = h_args;
-  c.h_margs = h_margs;
-  c.h_ctrl = h_ctrl;
+  c.h_blk = &h_blk;
   // twiddle tables (the largest supported length is 4096), as for a context
   static thread_local T tw[2][6 * 4096];
   const size_t sx = make_table(tw[0], c.nx), sy = make_table(tw[1], c.ny);
@@ -1182,8 +1212,8 @@ template <class T>
 wf_status fft_t(Ctx* c, const void* src, void* dst, bool forward, hipStream_t st) {
   Chain ch;
   SweepArgs<T> a = sweep_args<T>(c, nullptr, ch);
-  std::memcpy(c->h_args, &a, sizeof(a));
-  WF_TRY(hipMemcpyAsync(c->d_args, c->h_args, sizeof(a), hipMemcpyHostToDevice, st));
+  std::memcpy(c->h_blk->args, &a, sizeof(a));
+  WF_TRY(hipMemcpyAsync(c->d_args, c->h_blk->args, sizeof(a), hipMemcpyHostToDevice, st));
   const SweepArgs<T>* argv = (const SweepArgs<T>*)c->d_args;
   if (forward) {
     WF_TRY(launch_row<T>(kTileDefault, ROW_R2C, a, argv, 1, 0, (const T*)src, nullptr, st));
