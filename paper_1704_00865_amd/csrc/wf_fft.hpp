@@ -87,6 +87,14 @@ __device__ __forceinline__ cx<T> w16(int j) {
   return INV ? cx<T>{c, s} : cx<T>{c, -s};
 }
 
+// a w_16^j (j a compile-time constant once unrolled): a quarter turn is a swap,
+// where a product with (0, 1) would cost four operations that the compiler may
+// not drop
+template <class T, bool INV>
+__device__ __forceinline__ cx<T> mul_w16(cx<T> a, int j) {
+  return j == 4 ? mul_w4<T, INV>(a) : cmul(a, w16<T, INV>(j));
+}
+
 template <class T, bool INV>
 __device__ __forceinline__ void dft2(cx<T>* u) {
   const cx<T> a = u[0], b = u[1];
@@ -115,7 +123,7 @@ __device__ __forceinline__ void dft8(cx<T>* u) {
   dft4<T, INV>(y0);
   dft4<T, INV>(y1);
 #pragma unroll
-  for (int k1 = 1; k1 < 4; ++k1) y1[k1] = cmul(y1[k1], w16<T, INV>(2 * k1));
+  for (int k1 = 1; k1 < 4; ++k1) y1[k1] = mul_w16<T, INV>(y1[k1], 2 * k1);
 #pragma unroll
   for (int k1 = 0; k1 < 4; ++k1) {
     u[k1] = y0[k1] + y1[k1];
@@ -138,7 +146,7 @@ __device__ __forceinline__ void dft16(cx<T>* u) {
 #pragma unroll
   for (int n2 = 1; n2 < 4; ++n2)
 #pragma unroll
-    for (int k1 = 1; k1 < 4; ++k1) y[n2][k1] = cmul(y[n2][k1], w16<T, INV>(n2 * k1));
+    for (int k1 = 1; k1 < 4; ++k1) y[n2][k1] = mul_w16<T, INV>(y[n2][k1], n2 * k1);
 #pragma unroll
   for (int k1 = 0; k1 < 4; ++k1) {
     cx<T> a0 = y[0][k1], a1 = y[1][k1], a2 = y[2][k1], a3 = y[3][k1];

@@ -556,25 +556,25 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
     if constexpr (LTW) tws.store(twl, tid);
     __syncthreads();
     // Z = A + i B for the row pair; A, B Hermitian in k_x; slot 0 packs
-    // (re of k_x = 0, re of k_x = nx/2)
+    // (re of k_x = 0, re of k_x = nx/2).  Registers q < E/2 hold k < nx/2 and
+    // the others k >= nx/2, so only thread 0 of q = 0 and E/2 meets the packed
+    // slot
+    static_assert(E % 2 == 0, "half of the registers on either side of nx/2");
 #pragma unroll
     for (int q = 0; q < E; ++q) {
       const int k = t + NT * q;
-      const bool hi = k > NX / 2;
-      const int kx = hi ? NX - k : k;
-      const int ks = (kx == NX / 2) ? 0 : kx;
+      int ks = q < E / 2 ? k : NX - k;
+      if (q == E / 2) ks = t == 0 ? 0 : ks;
       const int li = (2 * p) * RS + ks;
       cx<T> A = lds[li], Bv = lds[li + RS];
-      if (kx == 0) {
-        A.im = (T)0;
-        Bv.im = (T)0;
-      } else if (kx == NX / 2) {
-        A = cx<T>{A.im, (T)0};
-        Bv = cx<T>{Bv.im, (T)0};
-      }
-      if (hi) {
+      if (q >= E / 2) {
         A.im = -A.im;
         Bv.im = -Bv.im;
+      }
+      if (q == 0 && t == 0) A.im = Bv.im = (T)0;
+      if (q == E / 2 && t == 0) {
+        A = cx<T>{-A.im, (T)0};
+        Bv = cx<T>{-Bv.im, (T)0};
       }
       reg[q] = cx<T>{A.re - Bv.im, A.im + Bv.re};
     }
@@ -628,7 +628,11 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
     if (jdo && tid == 0) gmem(a.jpart)[blk] = sum_partials(jsh, blockDim.x);
   }
   // split Z into the two rows' spectra; write this block's rows, tile order
-  for (int e = tid * EPC; e < SUB; e += blockDim.x * EPC) {
+  // (unrolled below 1024 points only: 12 to 20 registers more, a wave per SIMD
+  // less, which a full chip feels)
+#pragma unroll(NX < 1024 && E == 4 ? E / EPC : 1)
+  for (int it = 0; it < SUB / (NTHR * EPC); ++it) {
+    const int e = (tid + it * NTHR) * EPC;
     cx<T> v[EPC];
 #pragma unroll
     for (int u = 0; u < EPC; ++u) {
@@ -710,6 +714,11 @@ __device__ __forceinline__ cx<T> chain_d0(const ChainCoef<T>& k, T s, T nbA, cx<
   return k.first ? tAo : (n > big ? tBo : d);
 }
 
+// a/x + b/y + c/z in one division (about forty instructions in float64)
+__device__ __forceinline__ double sum3(double a, double x, double b, double y, double c, double z) {
+  return (a * (y * z) + b * (x * z) + c * (x * y)) / (x * y * z);
+}
+
 // One mode: t_2 (white messenger, Fourier) in, field for the white level out.
 // Reads and writes the stored Fourier-side fields of this mode.  pst: the
 // stripe variance of a mode on the k_x = 0 column, else 0.  With JV, adds
@@ -735,9 +744,9 @@ __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>
     stc(tB + idx, tBn);
     stc(tA + idx, tAn);
     if constexpr (JV)
-      jacc += jw * (cnorm2(tAn) / ((double)s + k.jTA) + cdist2(dAn, tAn) / (double)nbA +
-                     cdist2(tBn, dAn) / k.jTB + cdist2(dBn, tBn) / (double)nbB +
-                     cdist2(t2, dBn) / k.jTW);
+      jacc += jw * (sum3(cnorm2(tAn), (double)s + k.jTA, cdist2(dAn, tAn), (double)nbA,
+                         cdist2(tBn, dAn), k.jTB) +
+                     sum3(cdist2(dBn, tBn), (double)nbB, cdist2(t2, dBn), k.jTW, 0.0, 1.0));
     return dBn;
   } else {
     // one Fourier level: an array level or the stripe level
@@ -749,8 +758,8 @@ __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>
     const cx<T> tAn = wavg(k.TA, dAn, nb, so, rcp(nb + k.TA));
     stc(tA + idx, tAn);
     if constexpr (JV)
-      jacc += jw * (cnorm2(tAn) / ((double)s + k.jTA) + cdist2(dAn, tAn) / (double)nb +
-                     cdist2(t2, dAn) / k.jTW);
+      jacc += jw * sum3(cnorm2(tAn), (double)s + k.jTA, cdist2(dAn, tAn), (double)nb,
+                        cdist2(t2, dAn), k.jTW);
     return dAn;
   }
 }
@@ -822,15 +831,16 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
   // k_y > NY/2 in these columns are not updated (readers take the mirrored
   // mode).
   constexpr int EH = E / 2;
-  auto slot_ky = [&](int q) { return t + NT * (packed && q >= EH ? q - EH : q); };
-  auto slot_idx = [&](int q) { return (size_t)(packed && q >= EH ? kxn : kxc) * NY + slot_ky(q); };
+  const int pky = packed ? NT * EH : 0;                       // k_y of a slot q >= E/2: less this
+  const int pix = packed ? kxn * NY - NT * EH : 0;            // its index: plus this
+  const int idx0 = kxc * NY + t;
   auto load_half = [&](int h) {
 #pragma unroll
     for (int q = 0; q < HB; ++q) {
-      const size_t idx = slot_idx(h + q);
+      const int idx = idx0 + NT * (h + q) + (h + q >= EH ? pix : 0);
       sv[q] = gsc[idx];
       nv[q] = needNb ? gnb[idx] : (T)0;
-      pv[q] = (needP && packed && h + q < EH) ? gps[slot_ky(h + q)] : (T)0;
+      pv[q] = (needP && h + q < EH && packed) ? gps[t + NT * (h + q)] : (T)0;
       ta[q] = hasA ? ldc(gtA + idx) : z0;
       tb[q] = hasB ? ldc(gtB + idx) : z0;
     }
@@ -923,7 +933,9 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
 #pragma unroll
         for (int q = 0; q < EH; ++q) {
           const int ky = t + NT * q;
-          const cx<T> zk = reg[q], zm = ky == 0 ? zk : lds[LM::at(NY - ky)];
+          const cx<T> zk = reg[q];
+          cx<T> zm = lds[LM::at(ky == 0 ? NY / 2 : NY - ky)];
+          if (ky == 0) zm = cx<T>{zk.re, zk.im};
           reg[q] = cx<T>{(zk.re + zm.re) * (T)0.5, (zk.im - zm.im) * (T)0.5};
           reg[q + EH] = cx<T>{(zk.im + zm.im) * (T)0.5, (zm.re - zk.re) * (T)0.5};
         }
@@ -991,12 +1003,13 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
       if constexpr (!EARLY) load_half(h);
 #pragma unroll
       for (int q = 0; q < HB; ++q) {
-        const size_t idx = slot_idx(h + q);
+        const size_t idx = (size_t)(idx0 + NT * (h + q) + (h + q >= EH ? pix : 0));
         // k_y and NY - k_y of a real column are one conjugate pair
         if (jdo)
           reg[h + q] = chain_mode<T, FK, JV>(gtA, gtB, k, idx, reg[h + q], sv[q], nv[q], pv[q],
                                              ta[q], tb[q], jacc,
-                                             packed && slot_ky(h + q) == 0 ? 1.0 : 2.0);
+                                             packed && t + NT * (h + q) - (h + q >= EH ? pky : 0) == 0 ? 1.0
+                                                                                                   : 2.0);
         else
           reg[h + q] = chain_mode<T, FK, false>(gtA, gtB, k, idx, reg[h + q], sv[q], nv[q], pv[q],
                                                 ta[q], tb[q], jacc, 0.0);
@@ -1085,7 +1098,9 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg[q];
   __syncthreads();
-  for (int e = tid * EPC; e < TC * NY; e += blockDim.x * EPC) {
+#pragma unroll(NY < 1024 && E == 4 ? E / EPC : 1)
+  for (int it = 0; it < E / EPC; ++it) {
+    const int e = (tid + it * NTHR) * EPC;
     const int yb = e / TRTC, w = e - yb * TRTC;
     cx<T> v[EPC];
 #pragma unroll
@@ -1144,7 +1159,9 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
         __syncthreads();
         // element e of this block: row y = e / TC, column g TC + e % TC; EPC
         // consecutive values share a monitor tile row (TC and kTCM even)
-        for (int e = tid * EPC; e < TC * NY; e += blockDim.x * EPC) {
+#pragma unroll(NY < 1024 && E == 4 ? E / EPC : 1)
+        for (int it = 0; it < E / EPC; ++it) {
+          const int e = (tid + it * NTHR) * EPC;
           const int y = e / TC, cc0 = e - y * TC;
           const int kx0 = g * TC + cc0;
           cx<T> v[EPC];
@@ -1250,7 +1267,9 @@ __global__ __launch_bounds__(kTCM * (NY / mon_elems<NY>())) void mon_col_kernel(
     for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg[q];
     __syncthreads();
     // 16-byte stores: EPC consecutive values of a tile
-    for (int e = tid * EPC; e < kTCM * NY; e += blockDim.x * EPC) {
+#pragma unroll(NY < 1024 && E == 4 ? E / EPC : 1)
+    for (int it = 0; it < E / EPC; ++it) {
+      const int e = (tid + it * (kTCM * NT)) * EPC;
       const int yb = e / TRTC, w = e - yb * TRTC;
       cx<T> v[EPC];
 #pragma unroll
@@ -1355,19 +1374,15 @@ __global__ __launch_bounds__(kRWM * (NX / mon_elems<NX>())) void mon_row_kernel(
   cx<T> reg[E];
 #pragma unroll
   for (int q = 0; q < E; ++q) {
+    // registers q < E/2 hold k < nx/2, the others k >= nx/2
     const int k = t + NT * q;
-    const bool hi = k > NX / 2;
-    const int kx = hi ? NX - k : k;
-    const int li = r * RSm + kx;
+    const int li = r * RSm + (q < E / 2 ? k : NX - k);
     cx<T> X = lds[li], Y = lds[kRWM * RSm + li];
-    if (kx == 0 || kx == NX / 2) {
-      X.im = (T)0;
-      Y.im = (T)0;
-    }
-    if (hi) {
+    if (q >= E / 2) {
       X.im = -X.im;
       Y.im = -Y.im;
     }
+    if ((q == 0 || q == E / 2) && t == 0) X.im = Y.im = (T)0;
     reg[q] = cx<T>{X.re - Y.im, X.im + Y.re};
   }
   __syncthreads();
