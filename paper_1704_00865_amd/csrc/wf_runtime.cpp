@@ -30,6 +30,12 @@ namespace {
 constexpr int kStatBlocks = 1024;  // blocks of the validation statistics (partials in c->part)
 constexpr int kRing = 4;   // pinned readback slots
 constexpr int kLag = 2;    // chunks between enqueue and the host's check
+// Chunks per graph of a solve that runs its whole budget (fixed schedule, no
+// tolerance): the GPU idles for some 10 us between two graphs (refined 512^2,
+// a check every 8 sweeps: 14.4 ms with one chunk per graph, 13.5 with four).  A
+// solve that may stop early keeps one: chunks enqueued past its end return at
+// once but cost some 80 us each.
+constexpr int kMulti = 4;
 constexpr int kProfSlots = 512;
 constexpr int kStaticCheck = 4;  // chunks between host checks without events
 
@@ -105,13 +111,15 @@ struct Ctx {
   size_t batch_dev_bytes = 0;
   void* batch_host = nullptr;
   size_t batch_host_bytes = 0;
-  // one chunk of the single-map solve recorded as a HIP graph on cap_stream,
-  // replayed for every chunk; valid for the (K, last sweep of the budget
+  // one chunk, and kMulti chunks, of the single-map solve recorded as HIP
+  // graphs on cap_stream and replayed; valid for the (K, last sweep of the budget
   // within a chunk, tiling, chain kind) it was recorded with
   hipStream_t cap_stream = nullptr;
-  hipGraph_t chunk_graph = nullptr;
-  hipGraphExec_t chunk_exec = nullptr;
-  int chunk_key[4] = {-1, -1, -1, -1};
+  struct ChunkGraph {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    int key[4] = {-1, -1, -1, -1};
+  } chunks[2];  // one chunk, kMulti chunks
 };
 
 // Every device buffer of a context with its size: take(&pointer, bytes) is
@@ -212,8 +220,10 @@ void free_ctx(Ctx* c) {
   if (c->h_blk) (void)hipHostFree(c->h_blk);
   for (auto& e : c->prof_ev)
     if (e) (void)hipEventDestroy(e);
-  if (c->chunk_exec) (void)hipGraphExecDestroy(c->chunk_exec);
-  if (c->chunk_graph) (void)hipGraphDestroy(c->chunk_graph);
+  for (auto& g : c->chunks) {
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    if (g.graph) (void)hipGraphDestroy(g.graph);
+  }
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   delete c;
 }
@@ -639,27 +649,29 @@ void fill_report(wf_report* rep, const DevSched& fin, const Chain& ch, const dou
   rep->phi = ch.phi;
 }
 
-// The chunk graph of a context for this solve: recorded on the context's
-// capture stream the first time (or when the key changed), then reused.  The
-// launches read everything that changes between solves from the device
-// argument blocks and schedule, so one recording serves every solve with
-// the same key.
+// The graph of n chunks (1 or kMulti) of a context for this solve: recorded on
+// the context's capture stream the first time (or when the key changed), then
+// reused.  The launches read everything that changes between solves from the
+// device argument blocks and schedule, so one recording serves every solve
+// with the same key.
 template <class T>
 wf_status chunk_graph(Ctx* c, std::vector<ShapeClass<T>>& cls, const std::vector<MapRun<T>>& runs,
-                      int K, hipGraphExec_t* out) {
+                      int K, int n, hipGraphExec_t* out) {
+  Ctx::ChunkGraph& cg = c->chunks[n > 1 ? 1 : 0];
   const int key[4] = {K, (runs[0].h.max_sweeps - 1) % K, c->tile, runs[0].a.fk};
-  if (c->chunk_exec && std::memcmp(key, c->chunk_key, sizeof(key)) == 0) {
-    *out = c->chunk_exec;
+  if (cg.exec && std::memcmp(key, cg.key, sizeof(key)) == 0) {
+    *out = cg.exec;
     return WF_OK;
   }
-  if (c->chunk_exec) (void)hipGraphExecDestroy(c->chunk_exec);
-  if (c->chunk_graph) (void)hipGraphDestroy(c->chunk_graph);
-  c->chunk_exec = nullptr;
-  c->chunk_graph = nullptr;
+  if (cg.exec) (void)hipGraphExecDestroy(cg.exec);
+  if (cg.graph) (void)hipGraphDestroy(cg.graph);
+  cg.exec = nullptr;
+  cg.graph = nullptr;
   if (!c->cap_stream) WF_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
   WF_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-  const wf_status es = enqueue_chunk<T>(cls, runs, (const CtrlArgs*)c->d_ctrl, 1, K, nullptr,
-                                        c->cap_stream);
+  wf_status es = WF_OK;
+  for (int i = 0; i < n && es == WF_OK; ++i)
+    es = enqueue_chunk<T>(cls, runs, (const CtrlArgs*)c->d_ctrl, 1, K, nullptr, c->cap_stream);
   hipGraph_t g = nullptr;
   const hipError_t ce = hipStreamEndCapture(c->cap_stream, &g);
   if (es != WF_OK) {
@@ -667,10 +679,10 @@ wf_status chunk_graph(Ctx* c, std::vector<ShapeClass<T>>& cls, const std::vector
     return es;
   }
   WF_TRY(ce);
-  c->chunk_graph = g;
-  WF_TRY(hipGraphInstantiate(&c->chunk_exec, g, nullptr, nullptr, 0));
-  std::memcpy(c->chunk_key, key, sizeof(key));
-  *out = c->chunk_exec;
+  cg.graph = g;
+  WF_TRY(hipGraphInstantiate(&cg.exec, g, nullptr, nullptr, 0));
+  std::memcpy(cg.key, key, sizeof(key));
+  *out = cg.exec;
   return WF_OK;
 }
 
@@ -737,32 +749,35 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
   DevSched fin{};
   // without profiling (whose events are recorded by the dispatches of the
   // first sweeps) every chunk is the replayed graph
-  hipGraphExec_t exec = nullptr;
-  if (!prof && !c->no_alloc) {
-    wf_status gs = chunk_graph<T>(c, cls, runs, K, &exec);
-    if (gs != WF_OK) return gs;
-  }
-  for (int ci = 0; ci < r.n_chunks; ++ci) {
-    if (exec) {
+  const bool graphs = !prof && !c->no_alloc;
+  // a solve that can only end with its budget
+  const bool full = s->kind == WF_SCHED_FIXED && s->rtol == 0;
+  for (int ci = 0; ci < r.n_chunks;) {
+    int m = 1;
+    if (graphs) {
+      if (full && r.n_chunks - ci >= kMulti) m = kMulti;
+      hipGraphExec_t exec = nullptr;
+      wf_status gs = chunk_graph<T>(c, cls, runs, K, m, &exec);
+      if (gs != WF_OK) return gs;
       WF_TRY(hipGraphLaunch(exec, st));
     } else {
       hipEvent_t* ev = (prof && ci < prof_chunks) ? &c->prof_ev[6 * ci] : nullptr;
       wf_status es = enqueue_chunk<T>(cls, runs, (const CtrlArgs*)c->d_ctrl, 1, K, ev, st);
       if (es != WF_OK) return es;
     }
-    launched = ci + 1;
+    ci += m;
+    launched = ci;
     if (!viewed) {
       // no pinned memory: every kStaticCheck chunks the host waits for the
       // stream and reads the device schedule
-      if ((ci + 1) % kStaticCheck == 0 && ci + 1 < r.n_chunks) {
+      if (ci % kStaticCheck == 0 && ci < r.n_chunks) {
         WF_TRY(hipMemcpyAsync(&fin, c->sch, sizeof(fin), hipMemcpyDeviceToHost, st));
         WF_TRY(hipStreamSynchronize(st));
         if (fin.done) break;
       }
-    } else if (ci >= kLag) {
+    } else if (ci > kLag && ci < r.n_chunks) {
       bool done = false;
-      WF_TRY(wait_progress(c->view, std::min((ci - kLag + 1) * (int64_t)K, (int64_t)s->max_sweeps), st,
-                           &done));
+      WF_TRY(wait_progress(c->view, (ci - kLag) * (int64_t)K, st, &done));
       if (done) break;
     }
   }
