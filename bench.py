@@ -127,11 +127,11 @@ def cooling_lambdas(n_cool, n_total, lam0=1.0e4):
 
 def column_bytes(ny, nx, esz=4):
     """Algorithmic HBM bytes of one column-kernel launch (three-level chain):
-    transit buffer read + write, t_1, d_0, t_0 read + write (complex), S and
-    Nbar_0 read (real), stripe spectrum (one value per row)."""
+    transit buffer read + write, t_1, t_0 read + write (complex; d_0 is formed
+    from them), S and Nbar_0 read (real), stripe spectrum (one value per row)."""
     nh = nx // 2 + 1
     cpx = 2 * esz
-    return ny * nh * (2 * cpx + 6 * cpx + 2 * esz) + ny * esz
+    return ny * nh * (2 * cpx + 4 * cpx + 2 * esz) + ny * esz
 
 
 def row_bytes(ny, nx, esz=4):

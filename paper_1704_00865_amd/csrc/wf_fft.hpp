@@ -3,7 +3,8 @@
 //
 // A transform of length N (a power of two from 64 to 4096, or 3 times one:
 // 384, 768, 1536) is spread over NT = N/E threads that each hold E complex
-// values (E = 16, or 12 when N has a factor 3).  Register q of thread t holds
+// values (E = 16 from 1024 points, 12 when N has a factor 3, 4 below 1024; the
+// float32 kernels from 1024 points choose 8).  Register q of thread t holds
 // element t + NT*q both before the first pass and after the last one (natural
 // order), so a transform can be followed by per-element work and by another
 // transform without any reshuffle, and its first loads and last stores are
@@ -11,8 +12,9 @@
 // computes, for butterfly i in [0, N/R):
 //     u_m = x[i + m N/R] * w_{pR}^{m (i mod p)},  U = DFT_R(u),
 //     y[(i - i mod p) R + (i mod p) + m p] = U_m,
-// the autosorting Stockham form (radix 16, 12, 8, 4, 2).  Twiddles w_N^j come from a table built in
-// double precision on the host and rounded once (no device sin/cos).
+// the autosorting Stockham form (radix 16, 12, 8, 4, 2).  Twiddles w_N^j come
+// from a table built in double precision on the host and rounded once (no
+// device sin/cos).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -271,8 +273,6 @@ template <> struct plan<4096> { static constexpr int r[5] = {16, 16, 16, 1, 1}; 
 template <> struct plan<384> { static constexpr int r[5] = {4, 4, 2, 12, 1}; };
 template <> struct plan<768> { static constexpr int r[5] = {4, 4, 4, 12, 1}; };
 template <> struct plan<1536> { static constexpr int r[5] = {4, 4, 4, 2, 12}; };
-
-constexpr int kE = 16;  // values per thread for power-of-two lengths
 
 // radix plan for a transform spread over E values per thread: the default
 // plan, or radices of at most E

@@ -442,13 +442,11 @@ template <class T, int N>
 constexpr int min_waves() {
   return (sizeof(T) == 4 && N % 3 == 0) ? 3 : 2;
 }
-// waves per SIMD the column kernel is built for: with 8 float32 values per
-// thread four, or three below 1024 points, where a launch does not fill the
-// chip and a batch of four modes is worth more than a fourth wave; else as
-// above
+// waves per SIMD the column kernel is built for: four with 8 float32 values per
+// thread, else as above
 template <class T, int N>
 constexpr int col_min_waves() {
-  return (sizeof(T) == 4 && col_elems<T, N>() == 8) ? (N < 1024 ? 3 : 4) : min_waves<T, N>();
+  return (sizeof(T) == 4 && col_elems<T, N>() == 8) ? 4 : min_waves<T, N>();
 }
 // the chunk's last sweep (joint objective and the monitor's column
 // transforms) runs once per chunk: one wave per SIMD fewer, so that its
@@ -808,13 +806,12 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
   constexpr int NTHR = TC * NT;  // threads of the block
 
   // per-mode state and coefficients of this column, loaded in batches of 8
-  // modes, or 4 where the registers are scarce (float64, 4096 points, or the
-  // short lengths' three waves per SIMD), or 2 with 8 values per thread from
-  // 1024 points (four waves per SIMD leave 128 registers) and with 12 float32
-  // values (three waves, 168 registers)
-  constexpr int HB = E == 4 ? 4 : ((E == 8 && NY >= 1024) || (E == 12 && sizeof(T) == 4))
+  // modes, or 4 where the registers are scarce (float64, 4096 points) and with
+  // 4 values per thread, or 2 with 8 values per thread (four waves per SIMD
+  // leave 128 registers) and with 12 float32 values (three waves, 168 registers)
+  constexpr int HB = (E == 8 || (E == 12 && sizeof(T) == 4))
                          ? 2
-                         : ((sizeof(T) == 8 || E == 8 || E % 8 != 0 || NY >= 4096) ? 4 : 8);
+                         : ((sizeof(T) == 8 || E % 8 != 0 || NY >= 4096) ? 4 : 8);
   static_assert(E % HB == 0, "batches split the thread's values evenly");
   constexpr bool hasA = FK != FK_NONE;
   constexpr bool hasB = FK == FK_ARRAY_STRIPE;

@@ -28,7 +28,7 @@ using namespace wf;
 namespace {
 
 constexpr int kStatBlocks = 1024;  // blocks of the validation statistics (partials in c->part)
-constexpr int kRing = 4;   // pinned readback slots
+constexpr int kRing = 4;   // pinned readback slots of a batch
 constexpr int kLag = 2;    // chunks between enqueue and the host's check
 // Chunks per graph of a solve that runs its whole budget (fixed schedule, no
 // tolerance): the GPU idles for some 10 us between two graphs (refined 512^2,
