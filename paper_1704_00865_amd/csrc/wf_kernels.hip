@@ -705,7 +705,12 @@ __device__ __forceinline__ cx<T> chain_d0(const ChainCoef<T>& k, T s, T nbA, cx<
   const T n = nbA * k.rTBp;
   const T u = s * k.rSAp < big ? s * k.rSAp : big;
   const T un = u * n, u1 = u + (T)1;
-  const T inv = rcp(un * (n + (T)1) + k.ab * u1);
+  const T den = un * (n + (T)1) + k.ab * u1;
+  T inv = rcp(den);
+  // (one Newton step on the hardware reciprocal: its error is the same every
+  // sweep and both weights carry it; without the step float32 fields were 3%
+  // further from 64 bits than with d_0 stored, with it 3% closer, in the same time)
+  if constexpr (sizeof(T) == 4) inv = fmaf(fmaf(-den, inv, 1.0f), inv, inv);
   const T wb = (un * n) * inv, wa = ((n + k.ab) * u1) * inv;
   const cx<T> d = {wb * tBo.re + wa * tAo.re, wb * tBo.im + wa * tAo.im};
   // a start holds the same field in both
