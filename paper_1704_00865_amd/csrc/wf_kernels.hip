@@ -458,16 +458,19 @@ constexpr int col_waves() {
 }
 
 // Maps of a batch end at different sweeps, and the blocks of those that have
-// ended must not load what they will not use: in a batch the schedule is read
-// before the loads (218.6 to 48.1 us per sweep of 64 float64 1024^2 maps of
-// which one still runs; 10.84 to 11.29 ms for 100 sweeps of sixteen float32
-// 1024^2 maps that all do).  A single map reads it after them, off the latency chain.
-__device__ __forceinline__ bool batch_map_ended(const WF_GLOBAL DevSched* s, int k_local) {
-  return gridDim.y > 1 && (s->done || s->base + k_local >= s->max_sweeps);
+// ended must not load what they will not use: in a batch of more than one map
+// the schedule is read before the loads (219 to 48 us per sweep of 64 float64
+// 1024^2 maps of which one still runs, and 51 to 27 ms for 1600 sweeps of a 64^2
+// map beside an ended float32 4096^2 one; sixteen float32 1024^2 maps that all
+// run take 11.0 ms per 100 sweeps, and 11.2 without the early read).  A single map
+// reads it after them, off the latency chain.  batch is an argument of the launch:
+// read from the argument block it held a lone 64^2 map back by 0.09 us a sweep.
+__device__ __forceinline__ bool batch_map_ended(int batch, const WF_GLOBAL DevSched* s, int k_local) {
+  return batch && (s->done || s->base + k_local >= s->max_sweeps);
 }
 
 template <class T, int NX, int TR, int TC, int RW, int MODE>
-__global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T, NX>())) void row_kernel(const SweepArgs<T>* __restrict__ argv, int k_local,
+__global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T, NX>())) void row_kernel(const SweepArgs<T>* __restrict__ argv, int k_local, int batch,
     const T* __restrict__ xin, T* __restrict__ xout) {
   const SweepArgs<T>& a = argv[blockIdx.y];  // one map per grid row
   constexpr int E = row_elems<T, NX>();
@@ -530,7 +533,7 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
   };
 
   if constexpr (SW) {
-    if (batch_map_ended(gmem(a.sch), k_local)) return;
+    if (batch_map_ended(batch, gmem(a.sch), k_local)) return;
   }
   if constexpr (SW || MODE == ROW_C2R) {
     // every load of the band and of the twiddle table is issued before the
@@ -783,7 +786,7 @@ template <class T>
 __device__ __forceinline__ cx<T> cconj(cx<T> v) { return cx<T>{v.re, -v.im}; }
 
 template <class T, int NY, int TR, int TC, int MODE, int FK>
-__global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, MODE>())) void col_kernel(const SweepArgs<T>* __restrict__ argv, int k_local,
+__global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, MODE>())) void col_kernel(const SweepArgs<T>* __restrict__ argv, int k_local, int batch,
     cx<T>* __restrict__ spec, double lam_init) {
   const SweepArgs<T>& a = argv[blockIdx.y];  // one map per grid row
   constexpr int E = col_elems<T, NY>();
@@ -882,7 +885,7 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
     if constexpr (LTW) __syncthreads();
   } else {
     if constexpr (SW) {
-      if (batch_map_ended(gmem(a.sch), k_local)) return;
+      if (batch_map_ended(batch, gmem(a.sch), k_local)) return;
     }
     // every 16-byte load of this block's columns, then the twiddle table's,
     // is issued before the first LDS store (0.7 us faster at 2048^2 than

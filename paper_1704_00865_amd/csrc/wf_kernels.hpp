@@ -86,6 +86,8 @@ struct SweepArgs {
   void* Mx;               // monitor transit, tiled [y/kTRM][kx/kTCM][kTRM][kTCM]
   void* My;
   int32_t kpm;            // monitor transit columns (nx/2 + 1, padded to kTCM)
+  int32_t batch;          // other maps of the same call may sweep on after this one's end (the
+                          // sweep kernels get it as an argument of the launch)
 };
 
 // per-mode coefficient preparation (see prep_spectra_kernel)

@@ -925,6 +925,7 @@ wf_status solve_batch_t(Ctx** ctxs, int n, const wf_inputs* ins, const wf_schedu
     cl.argv = dargs + ha.size();
     cl.margv = dmargs + hm.size();
     for (int i : cl.maps) {
+      runs[i].a.batch = n > 1;  // whatever the size of its class
       ha.push_back(runs[i].a);
       hm.push_back(runs[i].m);
     }

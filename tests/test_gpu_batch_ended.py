@@ -1,0 +1,47 @@
+"""A map of a batch that has ended costs its batch next to nothing, also where
+no other map shares its shape: its blocks read that they have ended before
+they load anything."""
+
+import time
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _small():
+    import torch
+    p = synth.make_problem(64, 64, 3)
+    return {k: torch.tensor(np.ascontiguousarray(getattr(p, k)), dtype=torch.float32, device="cuda")
+            for k in ("d", "s_k", "n_pix", "p_oof", "p_stripe")}
+
+
+def _ends_at_once(n):
+    """White signal and uniform white noise: one sweep at lambda = 1 solves it."""
+    import torch
+    return dict(d=30.0 * torch.randn(n, n, device="cuda"),
+                s_k=torch.full((n, n // 2 + 1), 800.0, device="cuda"),
+                n_pix=torch.full((n, n), 100.0, device="cuda"))
+
+
+def test_ended_map_alone_in_its_class(gpu_lib):
+    """A 4096^2 map that ends at the first check beside a 64^2 map that runs its
+    whole budget.  Two such large maps form a class of two and do more work
+    than one does, so the batch with one may not take longer.  (It took 51 ms
+    instead of 31 when a class of one loaded its bands on every sweep.)"""
+    sched = gpu_lib.Schedule(lambdas=[1.0], rtol=1e-4, max_sweeps=1600, monitor_every=16)
+    best = {}
+    for k in (1, 2):
+        maps = [_ends_at_once(4096) for _ in range(k)] + [_small()]
+        ctxs = [gpu_lib.Context(*m["d"].shape, "f32") for m in maps]
+        for _ in range(4):
+            t0 = time.perf_counter()
+            _, reps = gpu_lib.solve_batch(ctxs, maps, schedule=sched)
+            dt = time.perf_counter() - t0
+            best[k] = min(best.get(k, dt), dt)
+            assert [r["sweeps"] for r in reps] == [16] * k + [1600]
+    print(f"one ended {best[1] * 1e3:.2f} ms, two {best[2] * 1e3:.2f}", flush=True)
+    assert best[1] <= best[2]
