@@ -34,8 +34,14 @@ constexpr int kLag = 2;    // chunks between enqueue and the host's check
 // tolerance): the GPU idles for some 10 us between two graphs (refined 512^2,
 // a check every 8 sweeps: 14.4 ms with one chunk per graph, 13.5 with four).  A
 // solve that may stop early keeps one: chunks enqueued past its end return at
-// once but cost some 80 us each.
+// once but cost some 80 us each.  Recording costs about 1.3 us per launch, that is
+// 10 (K + 1) us for kMulti chunks of K sweeps, and saves 10 us in three of four
+// chunks: a context's first solve of the kind records it only from 2 K chunks on
+// (64^2 float32, K = 16, 4 chunks: the first solve takes 0.13 ms longer than later
+// ones, 0.27 when it recorded four), and none does for long chunks, where the gaps
+// are below 3% of the time.
 constexpr int kMulti = 4;
+constexpr int kMultiSweeps = 32;  // longest chunk of which a graph holds kMulti
 constexpr int kProfSlots = 512;
 constexpr int kStaticCheck = 4;  // chunks between host checks without events
 
@@ -115,10 +121,17 @@ struct Ctx {
   // graphs on cap_stream and replayed; valid for the (K, last sweep of the budget
   // within a chunk, tiling, chain kind) it was recorded with
   hipStream_t cap_stream = nullptr;
+  struct ChunkKey {
+    int K, rest, tile, fk;
+    bool operator==(const ChunkKey& o) const {
+      return K == o.K && rest == o.rest && tile == o.tile && fk == o.fk;
+    }
+  };
   struct ChunkGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    int key[4] = {-1, -1, -1, -1};
+    ChunkKey key{};
+    bool holds(const ChunkKey& k) const { return exec && key == k; }
   } chunks[2];  // one chunk, kMulti chunks
 };
 
@@ -656,10 +669,9 @@ void fill_report(wf_report* rep, const DevSched& fin, const Chain& ch, const dou
 // with the same key.
 template <class T>
 wf_status chunk_graph(Ctx* c, std::vector<ShapeClass<T>>& cls, const std::vector<MapRun<T>>& runs,
-                      int K, int n, hipGraphExec_t* out) {
+                      const Ctx::ChunkKey& key, int n, hipGraphExec_t* out) {
   Ctx::ChunkGraph& cg = c->chunks[n > 1 ? 1 : 0];
-  const int key[4] = {K, (runs[0].h.max_sweeps - 1) % K, c->tile, runs[0].a.fk};
-  if (cg.exec && std::memcmp(key, cg.key, sizeof(key)) == 0) {
+  if (cg.holds(key)) {
     *out = cg.exec;
     return WF_OK;
   }
@@ -671,7 +683,7 @@ wf_status chunk_graph(Ctx* c, std::vector<ShapeClass<T>>& cls, const std::vector
   WF_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
   wf_status es = WF_OK;
   for (int i = 0; i < n && es == WF_OK; ++i)
-    es = enqueue_chunk<T>(cls, runs, (const CtrlArgs*)c->d_ctrl, 1, K, nullptr, c->cap_stream);
+    es = enqueue_chunk<T>(cls, runs, (const CtrlArgs*)c->d_ctrl, 1, key.K, nullptr, c->cap_stream);
   hipGraph_t g = nullptr;
   const hipError_t ce = hipStreamEndCapture(c->cap_stream, &g);
   if (es != WF_OK) {
@@ -681,7 +693,7 @@ wf_status chunk_graph(Ctx* c, std::vector<ShapeClass<T>>& cls, const std::vector
   WF_TRY(ce);
   cg.graph = g;
   WF_TRY(hipGraphInstantiate(&cg.exec, g, nullptr, nullptr, 0));
-  std::memcpy(cg.key, key, sizeof(key));
+  cg.key = key;
   *out = cg.exec;
   return WF_OK;
 }
@@ -750,14 +762,17 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
   // without profiling (whose events are recorded by the dispatches of the
   // first sweeps) every chunk is the replayed graph
   const bool graphs = !prof && !c->no_alloc;
-  // a solve that can only end with its budget
-  const bool full = s->kind == WF_SCHED_FIXED && s->rtol == 0;
+  // several chunks per graph: in a solve that can only end with its budget (see
+  // kMulti)
+  const Ctx::ChunkKey key{K, (s->max_sweeps - 1) % K, c->tile, r.a.fk};
+  const bool multi = s->kind == WF_SCHED_FIXED && s->rtol == 0 && K <= kMultiSweeps &&
+                     (c->chunks[0].holds(key) || r.n_chunks >= 2 * K);
   for (int ci = 0; ci < r.n_chunks;) {
     int m = 1;
     if (graphs) {
-      if (full && r.n_chunks - ci >= kMulti) m = kMulti;
+      if (multi && r.n_chunks - ci >= kMulti) m = kMulti;
       hipGraphExec_t exec = nullptr;
-      wf_status gs = chunk_graph<T>(c, cls, runs, K, m, &exec);
+      wf_status gs = chunk_graph<T>(c, cls, runs, key, m, &exec);
       if (gs != WF_OK) return gs;
       WF_TRY(hipGraphLaunch(exec, st));
     } else {
@@ -1458,7 +1473,10 @@ wf_status wf_autotune(void* ctx, const wf_inputs* in, int32_t sweeps, void* scra
   for (int tile = 0; tile < kNumTiles; ++tile) {
     if (ms) ms[tile] = -1.0;
     if (wf_ctx_set_tile(ctx, tile) != WF_OK) continue;
-    wf_status st = wf_solve(ctx, in, &sch, nullptr, scratch, nullptr, nullptr, stream);  // warm-up
+    // warm-up: records the graphs, that of several chunks in a second solve
+    wf_status st = wf_solve(ctx, in, &sch, nullptr, scratch, nullptr, nullptr, stream);
+    if (st >= 0 && sweeps >= kMulti * sch.monitor_every)
+      st = wf_solve(ctx, in, &sch, nullptr, scratch, nullptr, nullptr, stream);
     const auto t0 = std::chrono::steady_clock::now();
     for (int rep = 0; rep < 2 && st >= 0; ++rep)
       st = wf_solve(ctx, in, &sch, nullptr, scratch, nullptr, nullptr, stream);
