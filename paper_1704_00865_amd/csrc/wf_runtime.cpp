@@ -45,7 +45,7 @@ constexpr int kMultiSweeps = 32;  // longest chunk of which a graph holds kMulti
 constexpr int kProfSlots = 512;
 constexpr int kStaticCheck = 4;  // chunks between host checks without events
 
-constexpr int kViewRecords = 4096;   // monitor records kept in pinned memory
+constexpr int kViewRecords = 4096;   // most monitor records of a solve kept in pinned memory
 
 struct ArgBlock {
   alignas(16) unsigned char args[sizeof(SweepArgs<double>)];
@@ -90,7 +90,10 @@ struct Ctx {
   void* d_margs = nullptr;
   void* d_ctrl = nullptr;
   HostView* view = nullptr;    // pinned; null without allocations
-  double* h_trace = nullptr;   // pinned, kViewRecords records; written by the controller
+  // records of a single map's solve in pinned memory, written by the controller;
+  // allocated by the first such solve (a context that serves batches needs none)
+  double* h_trace = nullptr;
+  int h_trace_cap = 0;
   double* h_stats = nullptr;   // pinned
   int profiling = 0;
   std::vector<hipEvent_t> prof_ev;
@@ -271,8 +274,6 @@ wf_status create(const wf_shape* sh, Ctx** out) {
   hipError_t e = hipHostMalloc((void**)&c->view, sizeof(HostView), hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->h_stats, 16 * sizeof(double), hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->h_blk, sizeof(ArgBlock), hipHostMallocDefault);
-  if (e == hipSuccess)
-    e = hipHostMalloc((void**)&c->h_trace, kViewRecords * kTraceCols * sizeof(double), hipHostMallocDefault);
   if (e != hipSuccess) {
     free_ctx(c);
     return from_hip(e);
@@ -540,11 +541,21 @@ wf_status map_setup(Ctx* c, const wf_inputs* in, const wf_schedule* s, const voi
     if (as != WF_OK) return as;
     c->lam_cap = maxs + 1;
   }
-  if (c->trace_cap < r.n_chunks) {
+  // the records: in pinned memory where a single map's solve has few enough
+  const bool pinned = dsched == c->sch && c->view && r.n_chunks <= kViewRecords;
+  const size_t rec_bytes = (size_t)r.n_chunks * kTraceCols * sizeof(double);
+  if (pinned && c->h_trace_cap < r.n_chunks) {
+    if (c->h_trace) (void)hipHostFree(c->h_trace);
+    c->h_trace = nullptr;
+    c->h_trace_cap = 0;
+    WF_TRY(hipHostMalloc((void**)&c->h_trace, rec_bytes, hipHostMallocDefault));
+    c->h_trace_cap = r.n_chunks;
+  }
+  if (!pinned && c->trace_cap < r.n_chunks) {
     if (c->trace) (void)hipFree(c->trace);
     c->trace = nullptr;
     c->trace_cap = 0;
-    wf_status as = alloc((void**)&c->trace, (size_t)r.n_chunks * kTraceCols * sizeof(double));
+    wf_status as = alloc((void**)&c->trace, rec_bytes);
     if (as != WF_OK) return as;
     c->trace_cap = r.n_chunks;
   }
@@ -579,7 +590,8 @@ wf_status map_setup(Ctx* c, const wf_inputs* in, const wf_schedule* s, const voi
   r.m.sch = dsched;
   r.m.s_out = s_out;
   r.m.out_chain = s->field_mode;
-  r.ctrl = CtrlArgs{dsched, c->lam, c->part, c->ny / kRWM, c->trace, c->jpart, j_blocks(c), nullptr};
+  r.ctrl = CtrlArgs{dsched, c->lam, c->part, c->ny / kRWM, pinned ? c->h_trace : c->trace,
+                    c->jpart, j_blocks(c), nullptr};
   // initial state (the single-map argument block is used for the warm start)
   if (s_init) {
     std::memcpy(c->h_blk->args, &r.a, sizeof(r.a));
@@ -725,14 +737,11 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
   wf_status ss = map_setup<T>(c, in, s, s_init, s_out, c->sch, r, st);
   if (ss != WF_OK) return ss;
   if (chain_out) *chain_out = r.ch;
-  // argument blocks for the single-map launches; the records go to pinned
-  // memory where it holds them all
+  // argument blocks for the single-map launches
   const bool viewed = c->view != nullptr;
-  const bool view_trace = viewed && r.n_chunks <= kViewRecords;
   if (viewed) {
     c->view->progress = 0;
     r.ctrl.view = c->view;
-    if (view_trace) r.ctrl.trace = c->h_trace;
   }
   std::memcpy(c->h_blk->args, &r.a, sizeof(r.a));
   std::memcpy(c->h_blk->margs, &r.m, sizeof(r.m));
@@ -804,7 +813,7 @@ wf_status solve_t(Ctx* c, const wf_inputs* in, const wf_schedule* s, const void*
   if (viewed) fin = c->view->fin;
   if (trace && fin.n_rec > 0) {
     const size_t bytes = (size_t)fin.n_rec * kTraceCols * sizeof(double);
-    if (view_trace) std::memcpy(trace, c->h_trace, bytes);
+    if (r.ctrl.trace == c->h_trace) std::memcpy(trace, c->h_trace, bytes);
     else WF_TRY(hipMemcpy(trace, c->trace, bytes, hipMemcpyDeviceToHost));
   }
 
