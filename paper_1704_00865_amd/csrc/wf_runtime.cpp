@@ -1195,6 +1195,12 @@ wf_status scratch_on_device(int dev, unsigned char** out) {
 
 constexpr size_t kCarveAlign = 256;
 
+// host staging of the two sides' twiddle tables, for both precisions: the longest
+// are one table of 4096 values (float32) and three of 2048 (float64)
+constexpr size_t kTableBytes =
+    std::max<size_t>(4096 * 2 * sizeof(float), 3 * 2048 * 2 * sizeof(double));
+alignas(16) thread_local unsigned char g_tables[2][kTableBytes];
+
 // Place every device buffer of c, then the schedule arrays, from base
 // (nullptr: only count).  Returns the bytes used.
 size_t carve_static(Ctx* c, unsigned char* base, int lam_cap, int trace_cap) {
@@ -1238,8 +1244,8 @@ wf_status solve_noalloc_t(const wf_shape* sh, const wf_inputs* in, const wf_sche
   ArgBlock h_blk;
   c.h_stats = h_stats;
   c.h_blk = &h_blk;
-  // twiddle tables (the largest supported length is 4096), as for a context
-  static thread_local T tw[2][6 * 4096];
+  // twiddle tables, as for a context
+  T* tw[2] = {(T*)g_tables[0], (T*)g_tables[1]};
   const size_t sx = make_table(tw[0], c.nx), sy = make_table(tw[1], c.ny);
   WF_TRY(hipMemcpyAsync(c.twx, tw[0], sx * 2 * sizeof(T), hipMemcpyHostToDevice, st));
   WF_TRY(hipMemcpyAsync(c.twy, tw[1], sy * 2 * sizeof(T), hipMemcpyHostToDevice, st));
