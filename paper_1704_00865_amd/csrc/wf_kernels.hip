@@ -689,7 +689,7 @@ struct ChainCoef {
   bool first;          // sweep 0: the stored fields are the start, not a sweep's
   int fk;
   bool store_first;
-  double jTW, jTA, jTB;  // lambda tau in float64, for the joint objective
+  double jTW, jTA, jrTW, jrTB;  // lambda tau in float64 or its reciprocal, for the joint objective
 };
 
 template <class T>
@@ -732,9 +732,15 @@ __device__ __forceinline__ cx<T> chain_d0(const ChainCoef<T>& k, T s, T nbA, cx<
   return k.first ? tAo : (n > big ? tBo : d);
 }
 
-// a/x + b/y + c/z in one division (about forty instructions in float64)
-__device__ __forceinline__ double sum3(double a, double x, double b, double y, double c, double z) {
-  return (a * (y * z) + b * (x * z) + c * (x * y)) / (x * y * z);
+// 1/x of a link's variance in the joint objective: the hardware's reciprocal and
+// two Newton steps (2^-24, 2^-48, below 2^-52), in five instructions where an IEEE
+// division takes eleven.  (One division for three links over the product of their
+// variances took as long, but left the double range from variances of 1e-103 and
+// 1e+103 on, where every quotient is well inside it.)
+__device__ __forceinline__ double inv_var(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  const double r1 = fma(fma(-x, r, 1.0), r, r);
+  return x > 0.0 ? fma(fma(-x, r1, 1.0), r1, r1) : r;
 }
 
 // One mode: t_2 (white messenger, Fourier) in, field for the white level out.
@@ -749,7 +755,7 @@ __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>
                                             double jw) {
   if constexpr (FK == FK_NONE) {
     if (k.store_first) stc(tA + idx, t2);
-    if constexpr (JV) jacc += jw * cnorm2(t2) / ((double)s + k.jTW);
+    if constexpr (JV) jacc += jw * (cnorm2(t2) * inv_var((double)s + k.jTW));
     return cscale(t2, s * rcp(s + k.TW));
   } else if constexpr (FK == FK_ARRAY_STRIPE) {
     const T nbB = k.nxr * pst + k.cB;
@@ -762,9 +768,9 @@ __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>
     stc(tB + idx, tBn);
     stc(tA + idx, tAn);
     if constexpr (JV)
-      jacc += jw * (sum3(cnorm2(tAn), (double)s + k.jTA, cdist2(dAn, tAn), (double)nbA,
-                         cdist2(tBn, dAn), k.jTB) +
-                     sum3(cdist2(dBn, tBn), (double)nbB, cdist2(t2, dBn), k.jTW, 0.0, 1.0));
+      jacc += jw * (cnorm2(tAn) * inv_var((double)s + k.jTA) + cdist2(dAn, tAn) * inv_var(nbA) +
+                    cdist2(tBn, dAn) * k.jrTB + cdist2(dBn, tBn) * inv_var(nbB) +
+                    cdist2(t2, dBn) * k.jrTW);
     return dBn;
   } else {
     // one Fourier level: an array level or the stripe level
@@ -776,8 +782,8 @@ __device__ __forceinline__ cx<T> chain_mode(WF_GLOBAL cx<T>* tA, WF_GLOBAL cx<T>
     const cx<T> tAn = wavg(k.TA, dAn, nb, so, rcp(nb + k.TA));
     stc(tA + idx, tAn);
     if constexpr (JV)
-      jacc += jw * sum3(cnorm2(tAn), (double)s + k.jTA, cdist2(dAn, tAn), (double)nb,
-                        cdist2(t2, dAn), k.jTW);
+      jacc += jw * (cnorm2(tAn) * inv_var((double)s + k.jTA) + cdist2(dAn, tAn) * inv_var(nb) +
+                    cdist2(t2, dAn) * k.jrTW);
     return dAn;
   }
 }
@@ -1015,7 +1021,8 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
     k.store_first = store_first;
     k.jTW = lam * a.tauW;
     k.jTA = lam * a.tauA;
-    k.jTB = lam * a.tauB;
+    k.jrTW = inv_var(k.jTW);
+    k.jrTB = inv_var(lam * a.tauB);
     // J only on the chunk's last sweep (block-uniform)
     const bool jdo = JV && store_first;
 #pragma unroll
