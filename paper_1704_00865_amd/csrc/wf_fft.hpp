@@ -289,9 +289,9 @@ template <> struct plan_for<1024, 8> { static constexpr int r0 = 8, r1 = 8, r2 =
 template <> struct plan_for<2048, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 4, r4 = 1; };
 template <> struct plan_for<4096, 8> { static constexpr int r0 = 8, r1 = 8, r2 = 8, r3 = 8, r4 = 1; };
 
-// Twiddle tables.  The natural table holds w_N^j (forward sign) at j; pass
-// (span P, radix R) reads it at j = m k N/(P R), so that the lanes of one read
-// fall on a few LDS banks.  The pass-major table of a radix plan holds, for
+// Twiddle tables.  The natural table holds w_N^j (forward sign) at j; of it pass
+// (span P, radix R) needs j = m k N/(P R), which the lanes of one read would find
+// on a few LDS banks or cache lines.  The pass-major table of a radix plan holds, for
 // every pass after the first in order, w_N^{m k N/(P R)} at
 // off + (m - 1) P + k (m = 1..R-1, k = 0..P-1): lanes with consecutive k read
 // consecutive entries.  It has N - R0 entries (the spans grow by the factor R,
@@ -363,10 +363,9 @@ __device__ __forceinline__ void stage_twiddles(cx<T>* twp, TW tw, int tid) {
 }
 
 // One Stockham pass.  reg: the thread's E values; lds: this transform's
-// padded exchange buffer; tw: the natural twiddle table (OFF < 0) or the
-// pass-major one, whose entries for this pass start at OFF.
-template <class T, int N, int R, int P, bool INV, bool LAST, int E = elems<N>::value, int OFF = -1,
-          class TW = const cx<T>*>
+// padded exchange buffer; tw: the pass-major twiddle table, whose entries for
+// this pass start at OFF.
+template <class T, int N, int R, int P, bool INV, bool LAST, int E, int OFF, class TW>
 __device__ __forceinline__ void stockham_pass(cx<T>* reg, cx<T>* lds, int t, TW tw) {
   constexpr int NT = N / E;
   constexpr int NB = E / R;
@@ -380,10 +379,9 @@ __device__ __forceinline__ void stockham_pass(cx<T>* reg, cx<T>* lds, int t, TW 
 #pragma unroll
     for (int m = 0; m < R; ++m) u[m] = reg[b + m * NB];
     if constexpr (P > 1) {
-      constexpr int STEP = N / (P * R);
 #pragma unroll
       for (int m = 1; m < R; ++m) {
-        cx<T> w = ldc(OFF >= 0 ? tw + (OFF + (m - 1) * P + k) : tw + m * k * STEP);
+        cx<T> w = ldc(tw + (OFF + (m - 1) * P + k));
         if (INV) w.im = -w.im;
         u[m] = cmul(u[m], w);
       }
@@ -408,36 +406,33 @@ __device__ __forceinline__ void stockham_pass(cx<T>* reg, cx<T>* lds, int t, TW 
 
 // Full transform of length N.  Every thread of the workgroup must call it
 // (it contains barriers); lds must hold ldsmap<T, N, E>::size elements per
-// transform and must not be in use by the caller.  tw is the natural
-// twiddle table, or the pass-major one of plan_for<N, E> when TWP.
-template <class T, int N, bool INV, int E = elems<N>::value, bool TWP = false,
-          class TW = const cx<T>*>
+// transform and must not be in use by the caller.  tw is the pass-major
+// table of plan_for<N, E>, in LDS or in memory.
+template <class T, int N, bool INV, int E, class TW>
 __device__ __forceinline__ void fft(cx<T>* reg, cx<T>* lds, int t, TW tw) {
   using PL = plan_for<N, E>;
   using O = twp_offsets<N, E>;
   constexpr int R0 = PL::r0, R1 = PL::r1, R2 = PL::r2, R3 = PL::r3, R4 = PL::r4;
   static_assert(R0 * R1 * R2 * R3 * R4 == N, "radix plan must multiply to N");
-  constexpr int F2 = TWP ? O::o2 : -1, F3 = TWP ? O::o3 : -1, F4 = TWP ? O::o4 : -1,
-                F5 = TWP ? O::o5 : -1;
   constexpr int P2 = R0 * R1, P3 = P2 * R2, P4 = P3 * R3;
   if constexpr (R2 == 1) {
-    stockham_pass<T, N, R0, 1, INV, false, E, -1, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R1, R0, INV, true, E, F2, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R0, 1, INV, false, E, 0, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R1, R0, INV, true, E, O::o2, TW>(reg, lds, t, tw);
   } else if constexpr (R3 == 1) {
-    stockham_pass<T, N, R0, 1, INV, false, E, -1, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R1, R0, INV, false, E, F2, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R2, P2, INV, true, E, F3, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R0, 1, INV, false, E, 0, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R1, R0, INV, false, E, O::o2, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R2, P2, INV, true, E, O::o3, TW>(reg, lds, t, tw);
   } else if constexpr (R4 == 1) {
-    stockham_pass<T, N, R0, 1, INV, false, E, -1, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R1, R0, INV, false, E, F2, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R2, P2, INV, false, E, F3, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R3, P3, INV, true, E, F4, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R0, 1, INV, false, E, 0, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R1, R0, INV, false, E, O::o2, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R2, P2, INV, false, E, O::o3, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R3, P3, INV, true, E, O::o4, TW>(reg, lds, t, tw);
   } else {
-    stockham_pass<T, N, R0, 1, INV, false, E, -1, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R1, R0, INV, false, E, F2, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R2, P2, INV, false, E, F3, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R3, P3, INV, false, E, F4, TW>(reg, lds, t, tw);
-    stockham_pass<T, N, R4, P4, INV, true, E, F5, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R0, 1, INV, false, E, 0, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R1, R0, INV, false, E, O::o2, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R2, P2, INV, false, E, O::o3, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R3, P3, INV, false, E, O::o4, TW>(reg, lds, t, tw);
+    stockham_pass<T, N, R4, P4, INV, true, E, O::o5, TW>(reg, lds, t, tw);
   }
 }
 

@@ -592,8 +592,8 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
       reg[q] = cx<T>{A.re - Bv.im, A.im + Bv.re};
     }
     __syncthreads();
-    if constexpr (LTW) fft<T, NX, true, E, true>(reg, lds + p * XS, t, (const cx<T>*)twl);
-    else fft<T, NX, true, E, true>(reg, lds + p * XS, t, twg + NX);
+    if constexpr (LTW) fft<T, NX, true, E>(reg, lds + p * XS, t, (const cx<T>*)twl);
+    else fft<T, NX, true, E>(reg, lds + p * XS, t, twg + NX);
     const T sc = (T)a.scale;
     if constexpr (MODE == ROW_C2R) {
 #pragma unroll
@@ -632,8 +632,8 @@ __global__ __launch_bounds__((RW / 2) * (NX / row_elems<T, NX>()), (min_waves<T,
     }
     if constexpr (LTW) __syncthreads();
   }
-  if constexpr (LTW) fft<T, NX, false, E, true>(reg, lds + p * XS, t, (const cx<T>*)twl);
-  else fft<T, NX, false, E, true>(reg, lds + p * XS, t, twg + NX);
+  if constexpr (LTW) fft<T, NX, false, E>(reg, lds + p * XS, t, (const cx<T>*)twl);
+  else fft<T, NX, false, E>(reg, lds + p * XS, t, twg + NX);
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[p * XS + LM::at_tq(t, q)] = reg[q];
   __syncthreads();
@@ -938,8 +938,8 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
 #pragma unroll
     for (int q = 0; q < E; ++q) reg[q] = lds[c * YS + LM::at_tq(t, q)];
     __syncthreads();
-    if constexpr (LTW) fft<T, NY, false, E, true>(reg, lds + c * YS, t, (const cx<T>*)twl);
-    else fft<T, NY, false, E, true>(reg, lds + c * YS, t, twg + NY);
+    if constexpr (LTW) fft<T, NY, false, E>(reg, lds + c * YS, t, (const cx<T>*)twl);
+    else fft<T, NY, false, E>(reg, lds + c * YS, t, twg + NY);
   }
 
   // packed column (block 0, column 0): split Z = C0 + i CN into the k_x = 0
@@ -1120,8 +1120,8 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
     if (store_first && tid == 0)
       gmem(a.jpart)[a.jrow + g] = sum_partials(jsh, blockDim.x) * a.scale;
   }
-  if constexpr (LTW) fft<T, NY, true, E, true>(reg, lds + c * YS, t, (const cx<T>*)twl);
-  else fft<T, NY, true, E, true>(reg, lds + c * YS, t, twg + NY);
+  if constexpr (LTW) fft<T, NY, true, E>(reg, lds + c * YS, t, (const cx<T>*)twl);
+  else fft<T, NY, true, E>(reg, lds + c * YS, t, twg + NY);
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg[q];
   __syncthreads();
@@ -1179,8 +1179,8 @@ __global__ __launch_bounds__(TC * (NY / col_elems<T, NY>()), (col_waves<T, NY, M
       for (int field = 0; field < 2; ++field) {
         cx<T>* reg2 = field == 0 ? rx : ry;
         WF_GLOBAL cx<T>* dst = gmem((cx<T>*)(field == 0 ? a.Mx : a.My));
-        if constexpr (LTW) fft<T, NY, true, E, true>(reg2, lds + c * YS, t, (const cx<T>*)twl);
-        else fft<T, NY, true, E, true>(reg2, lds + c * YS, t, twg + NY);
+        if constexpr (LTW) fft<T, NY, true, E>(reg2, lds + c * YS, t, (const cx<T>*)twl);
+        else fft<T, NY, true, E>(reg2, lds + c * YS, t, twg + NY);
 #pragma unroll
         for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg2[q];
         __syncthreads();
@@ -1288,8 +1288,8 @@ __global__ __launch_bounds__(kTCM * (NY / mon_elems<NY>())) void mon_col_kernel(
   for (int field = 0; field < 2; ++field) {
     cx<T>* reg = field == 0 ? rx : ry;
     WF_GLOBAL cx<T>* dst = gmem((cx<T>*)(field == 0 ? m.Mx : m.My));
-    if constexpr (LTW) fft<T, NY, true, E, true>(reg, lds + c * YS, t, (const cx<T>*)twl);
-    else fft<T, NY, true, E, true>(reg, lds + c * YS, t, twg + 2 * NY);
+    if constexpr (LTW) fft<T, NY, true, E>(reg, lds + c * YS, t, (const cx<T>*)twl);
+    else fft<T, NY, true, E>(reg, lds + c * YS, t, twg + 2 * NY);
 #pragma unroll
     for (int q = 0; q < E; ++q) lds[c * YS + LM::at_tq(t, q)] = reg[q];
     __syncthreads();
@@ -1413,8 +1413,8 @@ __global__ __launch_bounds__(kRWM * (NX / mon_elems<NX>())) void mon_row_kernel(
     reg[q] = cx<T>{X.re - Y.im, X.im + Y.re};
   }
   __syncthreads();
-  if constexpr (LTW) fft<T, NX, true, E, true>(reg, lds + r * XS, t, (const cx<T>*)twl);
-  else fft<T, NX, true, E, true>(reg, lds + r * XS, t, twg + 2 * NX);
+  if constexpr (LTW) fft<T, NX, true, E>(reg, lds + r * XS, t, (const cx<T>*)twl);
+  else fft<T, NX, true, E>(reg, lds + r * XS, t, twg + 2 * NX);
   double a_dd = 0.0, a_mx = 0.0;
 #pragma unroll
   for (int q = 0; q < E; ++q) {
