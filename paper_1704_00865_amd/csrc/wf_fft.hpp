@@ -3,8 +3,9 @@
 //
 // A transform of length N (a power of two from 64 to 4096, or 3 times one:
 // 384, 768, 1536) is spread over NT = N/E threads that each hold E complex
-// values (E = 16 from 1024 points, 12 when N has a factor 3, 4 below 1024; the
-// float32 kernels from 1024 points choose 8).  Register q of thread t holds
+// values (E = 16 from 1024 points, 12 when N has a factor 3, 4 below 1024; from
+// 1024 points on the monitor's kernels choose 8, and so do the float32 row
+// kernels and, up to 2048, the float32 column kernels).  Register q of thread t holds
 // element t + NT*q both before the first pass and after the last one (natural
 // order), so a transform can be followed by per-element work and by another
 // transform without any reshuffle, and its first loads and last stores are

@@ -69,8 +69,10 @@ struct SweepArgs {
   const T* pst;           // [ny] stripe mode variance (caller's array)
   const T* d;             // [ny][nx] data (caller's array)
   const T* nbar2;         // [ny][nx] Nbar of the white level, < 0 where masked
-  const void* twx;        // w_nx^j table, cx<T>
-  const void* twy;        // w_ny^j table, cx<T>
+  // twiddle_tables(n, sizeof(T)) tables of n values, cx<T>: w_n^j in natural order,
+  // then, for the lengths that have them, the sweep's and the monitor's pass-major ones
+  const void* twx;
+  const void* twy;
   const DevSched* sch;
   const double* lam;      // lambda per sweep index
   int32_t nx, ny;
@@ -119,7 +121,7 @@ struct MonArgs {
   double nw_off;        // white variance = nbar2 + nw_off on observed pixels
   void* Mx;             // cx<T> monitor transit, tiled [y/kTRM][kx/kTCM][kTRM][kTCM]
   void* My;
-  const void* twx;      // cx<T> twiddle tables (natural order)
+  const void* twx;      // twiddle tables, as in SweepArgs
   const void* twy;
   const DevSched* sch;
   const double* lam;
