@@ -23,6 +23,10 @@
  *     the covariance of a real field does;
  *   - the stripe covariance is the variance of each unitary 1-D DFT mode of
  *     the row value f(y), [ny] in FFT order (stripe map n(x, y) = f(y));
+ *   - units: variances of order one to a hundred (a CMB map in uK) suit the
+ *     output's and the residual's transforms; in much smaller units (a map in
+ *     K) float32 outputs lose their digits, in much larger ones float32
+ *     residuals do;
  *   - sizes: nx, ny powers of two in [64, 4096] (FP64 path: up to 2048), or
  *     384, 768, 1536 (a radix-3 pass); other sizes give WF_EUNSUPPORTED;
  *   - every pointer in wf_inputs, s_init and s_out is a DEVICE pointer owned
